@@ -5,22 +5,37 @@
 // rescaled by a per-output-channel multiplier m and a right shift n with round to
 // nearest (ties up), and clamped to the symmetric int8 grid.
 //
-// Kernel shape: one workgroup of WN x WM waves computes a TN (channels) x TM (tokens)
-// tile with v_mfma_i32_32x32x32_i8; the waves form a WN x WM grid of (TN/WN) x (TM/WM)
-// sub-tiles.  K advances in 128-byte steps, so every global row segment is a whole
-// cache line.  The weights are stored in MFMA operand-fragment order (each 32-channel x
-// 32-byte fragment a contiguous 1 KB block in lane order), so every wave loads its own
-// weight fragments straight into registers with fully coalesced 16-byte loads, one K
-// step ahead.  The token tile is fetched into registers one step ahead (two for the
-// small output-projection tiles) and staged in LDS, whose rows are 128 bytes with the eight 16-byte chunks XOR-swizzled by the row
-// index, which keeps both the 16-byte stores of the fetch and the 16-byte MFMA operand
-// reads free of bank conflicts.
+// Kernel shape: one workgroup of four (or eight) waves computes a TN (channels) x TM (tokens) tile with
+// v_mfma_i32_32x32x32_i8; the waves form a WN x WM grid of (TN/WN) x (TM/WM) sub-tiles.  K
+// advances in 128-byte steps, so every global row segment is a whole cache line.  The
+// weights are stored in MFMA operand-fragment order (each 32-channel x 32-byte fragment a
+// contiguous 1 KB block in lane order), so every wave loads its own weight fragments
+// straight into registers with fully coalesced 16-byte loads, each slice's registers
+// refilled for the next step as soon as its MFMAs have read them.  The token tile is
+// fetched into registers one step ahead and staged in one of two LDS buffers, whose rows are
+// 128 bytes with the eight 16-byte chunks XOR-swizzled by the row index, which keeps both
+// the 16-byte stores of the fetch and the 16-byte MFMA operand reads free of bank
+// conflicts.
 //
-// The large projections use 256 x 256 tiles of eight waves (two per SIMD, 64 channels x
-// 128 tokens each, accumulators in VGPRs).  Per K step a workgroup then moves 32 KB of
-// token tile and 128 KB of token fragments through LDS and streams 64 KB of weight
-// fragments (each block read by the two waves that share its channels); with both
-// operands staged in LDS the step moved 256 KB through LDS and ran about 17 % slower.
+// The step is one stream without branches: token fragments are read one 32-byte slice
+// ahead of the MFMAs that use them, the next token tile is stored to LDS behind the first
+// slice, and the step's only barrier sits ahead of the last slice, so that the first
+// fragments of the next step are read under that slice's MFMAs.  Loads past the last step
+// are sent out of their buffer's range (zeros, no traffic) instead of being branched
+// around: with branches the compiler merged the wait counts of their paths and every
+// other step waited for the loads issued just before it.
+//
+// A wave owns at most 64 x 128 outputs (accumulators in VGPRs, two waves per SIMD).  As
+// 256 x 128 tiles of four waves two workgroups share a CU, and one's first fetch, epilogue
+// and barriers run under the other's MFMAs: 23000 tokens x 1024 -> 4096 (with the Swish)
+// take 103 us and 23000 x 4096 -> 1024 88 - 92 us, 1.9 - 2.1 POP/s (a library product of 8192^3
+// random int8 reaches 2.3 POP/s on this card), where eight-wave 256 x 256 and 128 x 128 tiles
+// under the branching loop took 127 and 122 us.  The 256 x 256 tile of eight waves moves a
+// third less from L2 per product (two of its waves share each weight block): it is
+// the faster one where one such tile per CU does the whole launch, and leaves the chip a
+// higher clock for the kernel after it (2500 tokens, Q|K|V and position table: 15.1 us against
+// 16.9 us from first to last workgroup, and the attention core after it at 2.20 GHz instead
+// of 2.08 GHz on a card that runs into its power limit).
 //
 // Token tiles never straddle two utterances (each utterance is tiled on its own), so
 // every destination layout receives whole aligned 16-byte pieces.  Tiles are dealt
@@ -81,6 +96,7 @@ struct GemmArgs {
   // m_y y, 1, shift_r)) with z1 laid out as y
   const int8_t* z1;
   int m_z, m_y, shift_r;
+  int res_wide;  // the residual add takes its 64-bit form
   const uint8_t* swtab;  // EPI_SWISH: output byte of each biased code h + 128
 };
 
@@ -89,7 +105,7 @@ constexpr int BK = 128;  // bytes of K per step
 // Byte offset of 16-byte chunk c of LDS row r.  Rows are 128 bytes; the chunk index
 // is XORed with (r ^ r/8) mod 8, so any 16 consecutive rows (16-row aligned) that
 // read one logical chunk touch 16 distinct (row parity, chunk) bank groups.
-__device__ __forceinline__ int lds_off(int r, int c) { return r * BK + ((c ^ ((r ^ (r >> 3)) & 7)) << 4); }
+__device__ __forceinline__ int lds_off(int r, int c) { return r * BK + ((c ^ (r & 7) ^ ((r >> 3) & 3)) << 4); }
 
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>), in order
 template <typename F, int... I>
@@ -163,9 +179,31 @@ __device__ __forceinline__ void pack16(const int (&v)[16], uint32_t (&D)[4], con
 }
 
 // The residual add of Eq. 2 on 16 int8 pairs: clamp8(floor((m_z z + m_y y + 2^(n-1)) / 2^n)).
-// m_z z + m_y y is exact in int32 (multipliers below 2^23, |z|, |y| <= 128); the
-// rounding term and the shift (n <= 40) need 64 bits.
+// Narrow form (the host proves (m_z + m_y) 128 + 2^(n-1) < 2^31, n <= 31): two 24-bit
+// multiply-adds, a shift and a clamp per value.
 __device__ __forceinline__ v4i residual16(const v4i& y, const v4i& z, int m_z, int m_y, int shift) {
+  const int half = (int)(1u << (shift - 1));
+  v4i r;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    int q[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int yb = (y[w] << (24 - 8 * b)) >> 24, zb = (z[w] << (24 - 8 * b)) >> 24;
+      const int t = mad24_s(zb, m_z, half);
+      int u;
+      asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(u) : "v"(yb), "s"(m_y), "v"(t));
+      q[b] = min(max(u >> shift, -127), 127);
+    }
+    r[w] = (int)(__builtin_amdgcn_perm((uint32_t)q[1], (uint32_t)q[0], 0x0c0c0400u) |
+                 __builtin_amdgcn_perm((uint32_t)q[3], (uint32_t)q[2], 0x04000c0cu));
+  }
+  return r;
+}
+
+// The general form: m_z z + m_y y is exact in int32 (multipliers below 2^23, |z|, |y| <=
+// 128); the rounding term and the shift (n <= 40) take 64 bits.
+__device__ __forceinline__ v4i residual16_wide(const v4i& y, const v4i& z, int m_z, int m_y, int shift) {
   const long long half = 1ll << (shift - 1);
   v4i r;
 #pragma unroll
@@ -185,13 +223,11 @@ __device__ __forceinline__ v4i residual16(const v4i& y, const v4i& z, int m_z, i
 // WN x WM waves (NWAVE = WN WM) each own a (TN/WN) x (TM/WM) sub-tile.  The weights
 // come pre-packed in MFMA fragment order (wfrag_index): each wave streams its own
 // fragments from memory straight into registers, one K step ahead, and only the token
-// tile goes through LDS.  EPI: the epilogue of row-major outputs.  TPF: register sets of
-// the token tile in flight (2 fetches each step's tile two steps before it is stored, for
-// long K loops whose operands come from beyond the L2).  WIDE: some problem of the
-// launch takes the wide form of Eq. 7 (its code costs registers even where unused, so
-// launches in the fast form alone leave it out).
-template <int TN, int TM, int NWAVE, int WN, int EPI, int TPF, bool WIDE>
-__global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
+// tile goes through LDS.  EPI: the epilogue of row-major outputs.  WIDE: some problem of
+// the launch takes the wide form of Eq. 7 or of the residual add (its code costs registers
+// even where unused, so launches in the fast forms alone leave it out).
+template <int TN, int TM, int NWAVE, int WN, int EPI, bool WIDE>
+__global__ __launch_bounds__(64 * NWAVE, NWAVE == 8 ? 1 : 2) void gemm_i8_requant(GemmArgs args) {
   constexpr int NTH = 64 * NWAVE;
   constexpr int WM = NWAVE / WN;            // waves along M
   constexpr int WTN = TN / WN;              // channels per wave
@@ -239,13 +275,17 @@ __global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave % WN, wm = wave / WN;
 
-  if (tid < TN) {
-    const int c = min(n0 + tid, N - 1);
-    sreq[0][tid] = P.req[c];
-    sreq[1][tid] = P.req[N + c];
+  // the tile's Eq. 7 constants and the Swish table: requested ahead of the first operands,
+  // stored to LDS behind them (read after the K loop)
+  int rq0, rq1 = 0;
+  uint32_t swt = 0;
+  {
+    const int c = min(n0 + min(tid, TN - 1), N - 1);
+    rq0 = P.req[c];
+    if (WIDE) rq1 = P.req[N + c];
+    if (EPI == EPI_SWISH) swt = ((const uint32_t*)args.swtab)[tid & 63];
   }
   const int rq_wide = WIDE ? __builtin_amdgcn_readfirstlane(P.wide) : 0, rq_clamp = __builtin_amdgcn_readfirstlane(P.clamp);
-  if (EPI == EPI_SWISH && tid < 64) stab32[tid] = ((const uint32_t*)args.swtab)[tid];
 
   // thread -> (row, chunk) of the fetch: 8 threads cover one 128-byte row segment.
   // Raw buffer loads: rows past the end of the operand (their whole offset is in the
@@ -253,42 +293,38 @@ __global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
   const int fchunk = tid & 7, frow = tid >> 3;  // rows frow + FROWS r
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc((void*)P.w, (short)0, N * K, BUF_WORD3);
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(P.x + ((size_t)ub * rows + t0) * K), (short)0, (rows - t0) * K, BUF_WORD3);
+      (void*)(P.x + ((size_t)ub * rows + t0) * K), (short)0, min(rows - t0, TM) * K, BUF_WORD3);
   const int foff = frow * K + fchunk * 16;
 
   // the next step's token tile in registers
-  static_assert(TPF == 1 || TPF == 2, "token prefetch depth");
-  v4i rx[TPF][LX];
+  v4i rx[LX];
   // this wave's weight fragments of one K step (FN channel blocks x KSL slices, 1 KB
-  // each, the slices of a block contiguous), two steps in registers.  A slice past K
-  // (odd multiples of 64) meets zero tokens, so its contents do not matter; reads past
-  // the matrix return zeros.
-  v4i wf[2][FN][KSL];
+  // each, the slices of a block contiguous).  A slice past K (odd multiples of 64) meets
+  // zero tokens, so its contents do not matter: block and slice are held inside the matrix,
+  // and steps past the last are sent out of range by the per-lane offset.
+  v4i wf[FN][KSL];
+  const int nk = (K + BK - 1) / BK;
   const int cb0 = (n0 + wn * WTN) >> 5;  // first 32-channel block of this wave
-  auto wfetch = [&](int kt, auto set_tag) {
-    constexpr int SET = decltype(set_tag)::value;
+  auto wfetch = [&](int kt, auto ks_tag) {
+    constexpr int ks = decltype(ks_tag)::value;
+    const int voff = lane * 16 + (kt < nk ? 0 : 0x7f000000);
+    const int kc = min(kt * KSL + ks, (K >> 5) - 1);
 #pragma unroll
     for (int i = 0; i < FN; ++i) {
-      const int base = __builtin_amdgcn_readfirstlane(((cb0 + i) * (K >> 5) + kt * KSL) * 1024);
-#pragma unroll
-      for (int ks = 0; ks < KSL; ++ks)
-        wf[SET][i][ks] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wres, lane * 16 + ks * 1024, base, 0);
+      const int base = __builtin_amdgcn_readfirstlane((min(cb0 + i, (N >> 5) - 1) * (K >> 5) + kc) * 1024);
+      wf[i][ks] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wres, voff, base, 0);
     }
   };
   // K is a multiple of 64: the last step of an odd multiple fills its upper half with zeros
-  auto fetch = [&](int k0, int set) {
-    if (k0 + fchunk * 16 < K) {
+  auto fetch = [&](int k0) {
+    const int base = k0 + fchunk * 16 < K ? foff + k0 : 0x40000000;
 #pragma unroll
-      for (int r = 0; r < LX; ++r)
-        rx[set][r] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(xres, foff + FROWS * r * K + k0, 0, 0);
-    } else {
-#pragma unroll
-      for (int r = 0; r < LX; ++r) rx[set][r] = (v4i){};
-    }
+    for (int r = 0; r < LX; ++r)
+      rx[r] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(xres, base + FROWS * r * K, 0, 0);
   };
-  auto stash = [&](int buf, int set) {
+  auto stash = [&](int buf) {
 #pragma unroll
-    for (int r = 0; r < LX; ++r) *(v4i*)(sx[buf] + lds_off(frow + FROWS * r, fchunk)) = rx[set][r];
+    for (int r = 0; r < LX; ++r) *(v4i*)(sx[buf] + lds_off(frow + FROWS * r, fchunk)) = rx[r];
   };
 
   // waves whose channels are V produce the transposed product (tokens along MFMA rows)
@@ -303,54 +339,69 @@ __global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
 
   // operand fragments: lane l reads row (l % 32), 16 bytes at k = 32 ks + 16 (l / 32)
   const int frag_row = lane & 31, half = lane >> 5;
-  const int nk = (K + BK - 1) / BK;
   // the K loop, instantiated once per operand order so that the order is not a
   // branch inside it
   auto kloop = [&](auto swap_tag) {
     constexpr bool SWAP = decltype(swap_tag)::value;
-    auto mma = [&](const int buf, auto wset_tag) {
-      constexpr int WSET = decltype(wset_tag)::value;
+    const int frag0 = lds_off(wm * WTM + frag_row, half);
+    v4i bf[2][FM];
+    auto rd = [&](const int buf, auto ks_tag, const int to) {
+      const int8_t* fp = sx[buf] + (frag0 ^ (decltype(ks_tag)::value << 5));
 #pragma unroll
-      for (int ks = 0; ks < KSL; ++ks) {
-        v4i bf[FM];
-#pragma unroll
-        for (int j = 0; j < FM; ++j)
-          bf[j] = *(const v4i*)(sx[buf] + lds_off(wm * WTM + j * 32 + frag_row, 2 * ks + half));
+      for (int j = 0; j < FM; ++j) bf[to][j] = *(const v4i*)(fp + j * 32 * BK);
+    };
+    auto step = [&](int kt, auto ph) {
+      constexpr int P2 = decltype(ph)::value;
+      static_for<KSL>([&](auto ks_tag) {
+        constexpr int ks = decltype(ks_tag)::value;
+        if constexpr (ks == KSL - 1) {
+          __syncthreads();
+          rd(P2 ^ 1, std::integral_constant<int, 0>{}, (ks + 1) & 1);
+        } else {
+          rd(P2, std::integral_constant<int, ks + 1>{}, (ks + 1) & 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < FN; ++i)
 #pragma unroll
           for (int j = 0; j < FM; ++j)
-            acc[i][j] = SWAP ? __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[j], wf[WSET][i][ks], acc[i][j], 0, 0, 0)
-                             : __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[WSET][i][ks], bf[j], acc[i][j], 0, 0, 0);
-      }
-    };
-    // step k is multiplied out of LDS buffer k % 2 (and weight set k % 2) while step
-    // k + 1 (fetched into token set (k + 1) % TPF, TPF steps earlier) is stored into the
-    // other buffer; one barrier per step orders both.  Unrolled twice so that the weight
-    // and token sets are static.
-    wfetch(0, std::integral_constant<int, 0>{});
-    fetch(0, 0);
-    stash(0, 0);
-    if (nk > 1) {
-      fetch(BK, 1 % TPF);
-      wfetch(1, std::integral_constant<int, 1>{});
-    }
-    if (TPF == 2 && nk > 2) fetch(2 * BK, 0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; kt += 2) {
-      static_for<2>([&](auto ph) {
-        constexpr int P2 = decltype(ph)::value;  // (kt + P2) % 2
-        if (kt + P2 < nk) {
-          mma(P2, ph);
-          if (kt + P2 + 1 < nk) {
-            stash(P2 ^ 1, (P2 + 1) % TPF);
-            if (kt + P2 + 1 + TPF < nk) fetch((kt + P2 + 1 + TPF) * BK, (P2 + 1) % TPF);
-            if (kt + P2 + 2 < nk) wfetch(kt + P2 + 2, ph);
-          }
-          __syncthreads();
+            acc[i][j] = SWAP ? __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[ks & 1][j], wf[i][ks], acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[i][ks], bf[ks & 1][j], acc[i][j], 0, 0, 0);
+        wfetch(kt + 1, ks_tag);
+        if constexpr (ks == 0) {
+          stash(P2 ^ 1);
+          fetch((kt + 2) * BK);
         }
+        __builtin_amdgcn_sched_barrier(0);
       });
+    };
+    constexpr std::integral_constant<int, 0> P0{};
+    constexpr std::integral_constant<int, 1> P1{};
+    // the scheduling barriers keep the loads in the loop's own order, so that the waits at
+    // the loop's head count the same outstanding loads on entry as from its end
+    fetch(0);
+    __builtin_amdgcn_sched_barrier(0);
+    wfetch(0, P0);
+    __builtin_amdgcn_sched_barrier(0);
+    stash(0);
+    if (tid < TN) {
+      sreq[0][tid] = rq0;
+      if (WIDE) sreq[1][tid] = rq1;
     }
+    if (EPI == EPI_SWISH && tid < 64) stab32[tid] = swt;
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(BK);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<KSL - 1>([&](auto ks) { wfetch(0, std::integral_constant<int, decltype(ks)::value + 1>{}); });
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    rd(0, P0, 0);
+    int kt = 0;
+    for (; kt + 2 <= nk; kt += 2) {
+      step(kt, P0);
+      step(kt + 1, P1);
+    }
+    if (kt < nk) step(kt, P0);
   };
   if (vwave) kloop(std::true_type{});
   else kloop(std::false_type{});
@@ -384,13 +435,24 @@ __global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
     return ((size_t)(t >> 6) << (dks + 6)) + (size_t)((kk >> 4) << 10) + (((((t >> 4) & 3) << 4) + (kk & 15)) << 4) +
            (t & 15);
   };
+  // the residual input of the whole sub-tile, requested at once ahead of the requantization
+  // (one trip to memory instead of one per output piece)
+  v4i zv[EPI == EPI_RESID ? FN : 1][EPI == EPI_RESID ? FM : 1];
+  if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+    for (int i = 0; i < FN; ++i)
+#pragma unroll
+      for (int j = 0; j < FM; ++j) {
+        const int nb = n0 + wn * WTN + i * 32, t = tw0 + j * 32 + col;
+        if (nb < N && t < rows) zv[i][j] = *(const v4i*)(o_z1 + ((size_t)ub * rows + t) * N + nb + half * 16);
+      }
+  }
 #pragma unroll
   for (int i = 0; i < FN; ++i) {
     const int nl = wn * WTN + i * 32;  // first channel of this sub-tile, tile-local
     const int nb = n0 + nl;
     if (nb >= N) continue;
     int8_t* dst;
-    const int8_t* zsrc = nullptr;  // residual input, laid out as dst (row-major mode)
     int kk = 0;  // channel of the sub-tile's first row inside its head
     int hd = 0;  // its head
     if (mode == OUT_QKV) {
@@ -405,7 +467,6 @@ __global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
       kk = nb & DKm;
     } else {
       dst = o_y + (size_t)ub * rows * N + nb;
-      zsrc = o_z1 + (size_t)ub * rows * N + nb;
     }
     // the tile-local channel of element e: with rows as tokens (V^T) the column, else
     // row g * 8 + half * 4 + e' of element e = 4g + e'
@@ -463,8 +524,10 @@ __global__ __launch_bounds__(64 * NWAVE) void gemm_i8_requant(GemmArgs args) {
       // channels of one token
       const uint32_t joff = vwave ? ((uint32_t)(j >> 1) << (dks + 6)) + (uint32_t)(j & 1) * 512u : (uint32_t)j * jstep;
       if (tl + j * 32 < tmax) {
-        if (EPI == EPI_RESID)
-          out = residual16(out, *(const v4i*)(zsrc + (off0 + joff)), args.m_z, args.m_y, args.shift_r);
+        if constexpr (EPI == EPI_RESID) {
+          out = WIDE && args.res_wide ? residual16_wide(out, zv[i][j], args.m_z, args.m_y, args.shift_r)
+                                      : residual16(out, zv[i][j], args.m_z, args.m_y, args.shift_r);
+        }
         *(v4i*)(dst + (off0 + joff)) = out;
       }
     }
@@ -518,102 +581,141 @@ static void fill_dest(GemmArgs& a, const RunShape& rs, const Workspace& ws, int8
   a.p_base = rs.p_base;
 }
 
-template <int TN, int TM, int NWAVE, int WN, int EPI = EPI_PLAIN, int TPF = 1>
+template <int TN, int TM, int NWAVE, int WN, int EPI>
 static hipError_t launch_gemm(GemmArgs& a, int tiles, hipStream_t st, const LaunchEv& ev) {
   a.tiles_total = tiles;
   a.per_xcd = (tiles + 7) / 8;
-  const bool wide = a.prob[0].wide || (a.nprob > 1 && a.prob[1].wide);
-  return wide ? launch_kernel(gemm_i8_requant<TN, TM, NWAVE, WN, EPI, TPF, true>, dim3(8 * a.per_xcd), dim3(64 * NWAVE),
-                              0, st, ev, a)
-              : launch_kernel(gemm_i8_requant<TN, TM, NWAVE, WN, EPI, TPF, false>, dim3(8 * a.per_xcd),
-                              dim3(64 * NWAVE), 0, st, ev, a);
+  const bool wide = a.prob[0].wide || (a.nprob > 1 && a.prob[1].wide) || (EPI == EPI_RESID && a.res_wide);
+  return wide ? launch_kernel(gemm_i8_requant<TN, TM, NWAVE, WN, EPI, true>, dim3(8 * a.per_xcd), dim3(64 * NWAVE), 0,
+                              st, ev, a)
+              : launch_kernel(gemm_i8_requant<TN, TM, NWAVE, WN, EPI, false>, dim3(8 * a.per_xcd), dim3(64 * NWAVE), 0,
+                              st, ev, a);
 }
 
-// Token-tile height for a launch of `tiles_of(TM)` tiles: every tile of a launch runs at
-// once when the tiles fit the CUs, so a launch takes about (rounds over the CUs) x (one
-// tile's K loop, proportional to TM).  The smaller height wins only when it needs
-// fewer rounds x rows (ties keep the larger tile, which has less overhead per row).
-constexpr int kGemmCUs = 256;
-template <typename F>
-static int pick_tile_rows(int big, int small, F tiles_of) {
-  auto cost = [&](int tm) { return (long)((tiles_of(tm) + kGemmCUs - 1) / kGemmCUs) * tm; };
-  return cost(small) < cost(big) ? small : big;
-}
-
-// A tile shape of the projection launch (channels, tokens, waves, waves along channels,
-// token-tile prefetch depth).
-template <int TN_, int TM_, int NWAVE_, int WN_, int TPF_>
-struct ProjShape {
-  static constexpr int tn = TN_, tm = TM_, nwave = NWAVE_, wn = WN_, tpf = TPF_;
+// The tile shapes (channels x tokens; four waves, the first eight) and the time model that picks one
+// for a launch: ceil(tiles / CUs) tiles pass through the busiest CU, each costing `fixed`
+// (its first operands and the epilogue: plain, with the residual add, with the Swish) plus
+// `per_k` per 1024 bytes of K, in microseconds fitted to launches of 16 .. 23000 tokens with
+// K = 256 .. 4096 and N = 256 .. 4096 (median error 3 %, and nine picks of ten within 5 % of
+// the fastest shape).  Large tiles re-use their operands best, small ones spread a short
+// call over the chip: 125 tokens x 4096 -> 1024 take 7.8 us in 128 x 32 tiles and 27 us in
+// 256 x 128 ones, 23000 tokens 88 us in the latter and 170 us in the former; 2500 tokens
+// x 1024 -> 4096 are fastest in between (128 x 64, 15.9 us against 17.3 and 21.6 us).
+struct TileShape {
+  int tn, tm;
+  double fixed[3], per_k;
 };
+constexpr TileShape kTiles[] = {{256, 256, {4.5, 7.0, 5.5}, 10.2},
+                                {256, 128, {2.2, 4.1, 2.8}, 5.2},
+                                {256, 64, {1.3, 2.1, 1.45}, 2.9},
+                                {128, 64, {0.52, 0.78, 0.62}, 1.92},
+                                {64, 64, {0.39, 0.46, 0.41}, 1.47},
+                                {128, 32, {0.34, 0.43, 0.31}, 1.40}};
+constexpr int kGemmCUs = 256;
+
+template <int I, int EPI>
+static hipError_t launch_shape(GemmArgs& a, int tiles, hipStream_t st, const LaunchEv& ev) {
+  return launch_gemm<kTiles[I].tn, kTiles[I].tm, kTiles[I].tm == 256 ? 8 : 4, kTiles[I].tn == 64 ? 2 : 4, EPI>(a, tiles, st,
+                                                                                                               ev);
+}
+
+// Launches with the cheapest shape: tiles_of(tn, tm) counts a shape's tiles, fill(args, tn, tm)
+// adds the problems (all of contraction length K) and returns the same count.  min_tm: 64
+// where V^T is written (whole 64-key blocks).
+template <int EPI, typename Count, typename Fill>
+static hipError_t launch_best(int K, int min_tm, Count tiles_of, Fill fill, hipStream_t st, const LaunchEv& ev) {
+  int best = -1;
+  double best_t = 0.0;
+  for (int i = 0; i < 6; ++i) {
+    const TileShape& s = kTiles[i];
+    if (s.tm < min_tm) continue;
+    const double t = (double)((tiles_of(s.tn, s.tm) + kGemmCUs - 1) / kGemmCUs) * (s.fixed[EPI] + s.per_k * K / 1024.0);
+    if (best < 0 || t < best_t) {
+      best = i;
+      best_t = t;
+    }
+  }
+  GemmArgs a{};
+  const int tiles = fill(a, kTiles[best].tn, kTiles[best].tm);
+  switch (best) {
+    case 0: return launch_shape<0, EPI>(a, tiles, st, ev);
+    case 1: return launch_shape<1, EPI>(a, tiles, st, ev);
+    case 2: return launch_shape<2, EPI>(a, tiles, st, ev);
+    case 3: return launch_shape<3, EPI>(a, tiles, st, ev);
+    case 4: return launch_shape<4, EPI>(a, tiles, st, ev);
+    default: return launch_shape<5, EPI>(a, tiles, st, ev);
+  }
+}
+
+static long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
 hipError_t launch_projections(const RunShape& rs, const Weights& w, const Workspace& ws, const int8_t* x,
                               const int8_t* pos_table, hipStream_t st, const LaunchEv& ev) {
-  // 256-channel tiles of eight waves in a 4 x 2 grid (64 channels x TM/2 tokens each):
-  // with TM = 256, per K step a workgroup moves 32 KB of token tile and 128 KB of token
-  // fragments through LDS and streams 64 KB of weight fragments (each wave's own, two
-  // waves per block).  TM = 128 halves the tiles' height when that fills the CUs better
-  // (Q|K|V alone at T = 2500: 240 tiles in one round instead of 120 of twice the work).
-  constexpr int TN = 256, NWAVE = 8, WN = 4;
-  auto tiles_of = [&](int tm) {
-    long t = (long)rs.B * ((rs.T + tm - 1) / tm) * ((3 * rs.d + TN - 1) / TN);
-    if (pos_table) t += (long)((2 * rs.T - 1 + tm - 1) / tm) * ((rs.d + TN - 1) / TN);
+  auto tiles_of = [&](int tn, int tm) {
+    long t = rs.B * ceil_div(rs.T, tm) * ceil_div(3 * rs.d, tn);
+    if (pos_table) t += ceil_div(2 * rs.T - 1, tm) * ceil_div(rs.d, tn);
     return t;
   };
-  const int TMr = pick_tile_rows(256, 128, tiles_of);
-  auto go = [&](auto shape_tag) {
-    using S = decltype(shape_tag);
-    constexpr int TNs = S::tn, TMs = S::tm, NW = S::nwave, WNs = S::wn, TPFs = S::tpf;
-    // V^T's 64-key blocks: a wave's tokens are whole blocks
-    static_assert((TMs / (NW / WNs)) % KCHUNK == 0 && (TNs / WNs) % 32 == 0, "projection tile shape");
-    GemmArgs a{};
+  auto fill = [&](GemmArgs& a, int tn, int tm) {
     fill_dest(a, rs, ws, nullptr);
-    int tiles = add_problem(a, 0, x, w.w_qkv, w.rq_qkv, rs.B, rs.T, 3 * rs.d, rs.d, OUT_QKV, 0, TNs, TMs);
+    int tiles = add_problem(a, 0, x, w.w_qkv, w.rq_qkv, rs.B, rs.T, 3 * rs.d, rs.d, OUT_QKV, 0, tn, tm);
     a.nprob = 1;
     if (pos_table) {
-      tiles += add_problem(a, 1, pos_table, w.w_pos, w.rq_pos, 1, 2 * rs.T - 1, rs.d, rs.d, OUT_POS, tiles, TNs, TMs);
+      tiles += add_problem(a, 1, pos_table, w.w_pos, w.rq_pos, 1, 2 * rs.T - 1, rs.d, rs.d, OUT_POS, tiles, tn, tm);
       a.nprob = 2;
     }
-    return launch_gemm<TNs, TMs, NW, WNs, EPI_PLAIN, TPFs>(a, tiles, st, ev);
+    return tiles;
   };
-  // a short call (few frames): where the 256-channel tiles would leave more than half of
-  // the CUs idle, 128-channel x 64-token tiles of four waves (32 channels x 64 tokens
-  // each, the token tile fetched two steps ahead) spread it over several times as many
-  // workgroups
-  if (tiles_of(TMr) < kGemmCUs / 2) return go(ProjShape<128, 64, 4, 4, 2>{});
-  return TMr == 128 ? go(ProjShape<TN, 128, NWAVE, WN, 1>{}) : go(ProjShape<TN, 256, NWAVE, WN, 1>{});
+  return launch_best<EPI_PLAIN>(rs.d, KCHUNK, tiles_of, fill, st, ev);
 }
 
 hipError_t launch_pos_projection(const RunShape& rs, const Weights& w, int8_t* p, const int8_t* pos_table,
                                  hipStream_t st) {
-  GemmArgs a{};
   Workspace ws{};
   ws.p = p;
-  fill_dest(a, rs, ws, nullptr);
-  constexpr int TN = 256, TM = 256, NWAVE = 8, WN = 4;
-  const int tiles = add_problem(a, 0, pos_table, w.w_pos, w.rq_pos, 1, 2 * rs.T - 1, rs.d, rs.d, OUT_POS, 0, TN, TM);
-  a.nprob = 1;
-  return launch_gemm<TN, TM, NWAVE, WN>(a, tiles, st, LaunchEv{});
+  const int rows = 2 * rs.T - 1;
+  auto tiles_of = [&](int tn, int tm) { return ceil_div(rows, tm) * ceil_div(rs.d, tn); };
+  auto fill = [&](GemmArgs& a, int tn, int tm) {
+    fill_dest(a, rs, ws, nullptr);
+    a.nprob = 1;
+    return add_problem(a, 0, pos_table, w.w_pos, w.rq_pos, 1, rows, rs.d, rs.d, OUT_POS, 0, tn, tm);
+  };
+  return launch_best<EPI_PLAIN>(rs.d, 32, tiles_of, fill, st, LaunchEv{});
+}
+
+// A row-major product of nb x rows tokens (K -> N), `setup` filling the epilogue's arguments.
+template <int EPI, typename Setup>
+static hipError_t launch_rowmajor(const int8_t* x, int nb, int rows, int N, int K, const int8_t* w, const Requant& rq,
+                                  int8_t* y, Setup setup, hipStream_t st, const LaunchEv& ev) {
+  auto tiles_of = [&](int tn, int tm) { return nb * ceil_div(rows, tm) * ceil_div(N, tn); };
+  auto fill = [&](GemmArgs& a, int tn, int tm) {
+    a.y = y;
+    a.nprob = 1;
+    setup(a);
+    return add_problem(a, 0, x, w, rq, nb, rows, N, K, OUT_ROWMAJOR, 0, tn, tm);
+  };
+  return launch_best<EPI>(K, 32, tiles_of, fill, st, ev);
+}
+
+static void set_residual(GemmArgs& a, const int8_t* z, int m_z, int m_y, int shift_r) {
+  a.z1 = z;
+  a.m_z = m_z;
+  a.m_y = m_y;
+  a.shift_r = shift_r;
+  a.res_wide = shift_r > 31 || ((int64_t)m_z + m_y) * 128 + ((int64_t)1 << (shift_r - 1)) >= ((int64_t)1 << 31);
 }
 
 hipError_t launch_out_projection(const RunShape& rs, const Weights& w, const Workspace& ws, int8_t* y,
                                  hipStream_t st, const LaunchEv& ev, const Residual* res, const int8_t* z1) {
-  GemmArgs a{};
-  fill_dest(a, rs, ws, y);
-  if (res) {
-    a.z1 = z1;
-    a.m_z = res->m_z;
-    a.m_y = res->m_y;
-    a.shift_r = res->shift_r;
-  }
-  // small tiles (640 at T = 2500): with K = d_model and few 64-token blocks the launch
-  // is bound by load latency, and larger tiles measured no faster
-  constexpr int TN = 64, TM = 64, NWAVE = 4, WN = 2;
-  int tiles = add_problem(a, 0, ws.ctx, w.w_out, w.rq_out, rs.B, rs.T, rs.d, rs.d, OUT_ROWMAJOR, 0, TN, TM);
-  a.nprob = 1;
-  // the token tile two steps ahead: 0.6 - 0.7 us less per call at T = 2500 (interleaved A/B)
-  if (res) return launch_gemm<TN, TM, NWAVE, WN, EPI_RESID, 2>(a, tiles, st, ev);
-  return launch_gemm<TN, TM, NWAVE, WN, EPI_PLAIN, 2>(a, tiles, st, ev);
+  // the utterances' rows are contiguous on both sides, so tiles may straddle them (while the
+  // kernel's 32-bit offsets reach)
+  const bool flat = (int64_t)rs.B * rs.T * rs.d < ((int64_t)1 << 31);
+  const int nb = flat ? 1 : rs.B, rows = flat ? rs.B * rs.T : rs.T;
+  if (res)
+    return launch_rowmajor<EPI_RESID>(
+        ws.ctx, nb, rows, rs.d, rs.d, w.w_out, w.rq_out, y,
+        [&](GemmArgs& a) { set_residual(a, z1, res->m_z, res->m_y, res->shift_r); }, st, ev);
+  return launch_rowmajor<EPI_PLAIN>(ws.ctx, nb, rows, rs.d, rs.d, w.w_out, w.rq_out, y, [](GemmArgs&) {}, st, ev);
 }
 
 // ---------------------------------------------------------------------------
@@ -642,69 +744,19 @@ hipError_t launch_swish_table(uint8_t* tab, long long q_c, long long q_1, long l
 
 hipError_t launch_ffn_up(const int8_t* x, int rows, int d, int d_ff, const int8_t* w1, const Requant& rq1,
                          const uint8_t* swtab, int8_t* o, hipStream_t st) {
-  // 256-channel tiles of eight waves; 192-token tiles when they need no more rounds
-  // over the CUs than 256-token ones (2500 rows: 224 tiles instead of 160 of 4/3 the work)
-  constexpr int TN = 256, NWAVE = 8, WN = 4;
-  auto tiles_of = [&](int tm) { return (long)((rows + tm - 1) / tm) * ((d_ff + TN - 1) / TN); };
-  auto go = [&](auto tm_tag) {
-    constexpr int TM = decltype(tm_tag)::value;
-    GemmArgs a{};
-    a.y = o;
-    a.swtab = swtab;
-    const int tiles = add_problem(a, 0, x, w1, rq1, 1, rows, d_ff, d, OUT_ROWMAJOR, 0, TN, TM);
-    a.nprob = 1;
-    return launch_gemm<TN, TM, NWAVE, WN, EPI_SWISH>(a, tiles, st, LaunchEv{});
-  };
-  return pick_tile_rows(256, 192, tiles_of) == 192 ? go(std::integral_constant<int, 192>{})
-                                                   : go(std::integral_constant<int, 256>{});
+  return launch_rowmajor<EPI_SWISH>(x, 1, rows, d_ff, d, w1, rq1, o, [&](GemmArgs& a) { a.swtab = swtab; }, st,
+                                    LaunchEv{});
 }
 
 hipError_t launch_linear_resid(const int8_t* x, int rows, int N, int K, const int8_t* w, const Requant& rq,
                                const int8_t* z, int m_z, int m_y, int shift_r, int8_t* z_out, hipStream_t st) {
-  GemmArgs a{};
-  a.y = z_out;
-  a.z1 = z;
-  a.m_z = m_z;
-  a.m_y = m_y;
-  a.shift_r = shift_r;
-  // 128 x 128 tiles of eight waves (32 channels x 64 tokens each): for the feed-forward
-  // module's W2 (K = d_ff) measured against 64 x 64, 128 x 64, 128 x 96, 64 x 192,
-  // 256 x 128 and 128 x 256 tiles at 2500 and 4000 rows
-  constexpr int TN = 128, TM = 128, NWAVE = 8, WN = 4;
-  const int tiles = add_problem(a, 0, x, w, rq, 1, rows, N, K, OUT_ROWMAJOR, 0, TN, TM);
-  a.nprob = 1;
-  return launch_gemm<TN, TM, NWAVE, WN, EPI_RESID>(a, tiles, st, LaunchEv{});
+  return launch_rowmajor<EPI_RESID>(x, 1, rows, N, K, w, rq, z_out,
+                                    [&](GemmArgs& a) { set_residual(a, z, m_z, m_y, shift_r); }, st, LaunchEv{});
 }
 
 hipError_t launch_linear(const int8_t* x, int rows, int K, int N, const int8_t* w, const Requant& rq, int8_t* y,
                          hipStream_t st) {
-  constexpr int TN = 256, NWAVE = 8, WN = 4;
-  auto tiles_of = [&](int tm) { return (long)((rows + tm - 1) / tm) * ((N + TN - 1) / TN); };
-  int TMr = pick_tile_rows(256, 192, tiles_of);
-  TMr = pick_tile_rows(TMr, 128, tiles_of);
-  auto go = [&](auto tm_tag) {
-    constexpr int TM = decltype(tm_tag)::value;
-    GemmArgs a{};
-    a.y = y;
-    const int tiles = add_problem(a, 0, x, w, rq, 1, rows, N, K, OUT_ROWMAJOR, 0, TN, TM);
-    a.nprob = 1;
-    return launch_gemm<TN, TM, NWAVE, WN>(a, tiles, st, LaunchEv{});
-  };
-  // 128-channel x 192-token tiles (eight waves of 32 x 96) when they leave the busiest
-  // CU less work than the 256-channel shape picked above (2500 rows, N = 2048: 224 tiles
-  // of 24.6 K outputs against 160 of 32.8 K)
-  const long t128 = (long)((rows + 191) / 192) * ((N + 127) / 128);
-  const long rounds_wide = (tiles_of(TMr) + kGemmCUs - 1) / kGemmCUs, rounds128 = (t128 + kGemmCUs - 1) / kGemmCUs;
-  if (rounds128 * 128 * 192 < rounds_wide * TN * TMr) {
-    GemmArgs a{};
-    a.y = y;
-    const int tiles = add_problem(a, 0, x, w, rq, 1, rows, N, K, OUT_ROWMAJOR, 0, 128, 192);
-    a.nprob = 1;
-    return launch_gemm<128, 192, 8, 4>(a, tiles, st, LaunchEv{});
-  }
-  if (TMr == 128) return go(std::integral_constant<int, 128>{});
-  if (TMr == 192) return go(std::integral_constant<int, 192>{});
-  return go(std::integral_constant<int, 256>{});
+  return launch_rowmajor<EPI_PLAIN>(x, 1, rows, N, K, w, rq, y, [](GemmArgs&) {}, st, LaunchEv{});
 }
 
 // one thread per 16-byte piece of the destination
