@@ -184,6 +184,21 @@ static int build_requant(const int32_t* const* mults, const int32_t* shifts, int
   return 1;
 }
 
+// Uploads LayerNorm constants in the kernel's load order (Residual), the rounding term
+// folded into the biases.
+static hipError_t upload_ln(int32_t* g, int64_t* c, const int32_t* mult, const int64_t* bias, int shift, int d) {
+  std::vector<int32_t> hg(d);
+  std::vector<int64_t> hc(d);
+  const int np = d / 16;
+  for (int k = 0; k < d; ++k) {
+    const int p = k / 16, e = k % 16;
+    hg[((size_t)(e / 4) * np + p) * 4 + e % 4] = mult[k];
+    hc[((size_t)(e / 2) * np + p) * 2 + e % 2] = bias[k] + ((int64_t)1 << (shift - 1));
+  }
+  hipError_t e = hipMemcpy(g, hg.data(), d * sizeof(int32_t), hipMemcpyHostToDevice);
+  return e == hipSuccess ? hipMemcpy(c, hc.data(), d * sizeof(int64_t), hipMemcpyHostToDevice) : e;
+}
+
 // Builds and uploads a matrix's Eq. 7 constants into a device buffer of the handle.
 template <typename H>
 static hipError_t upload_requant(H* h, Requant* rq, const int32_t* const* mults, const int32_t* shifts, int parts,
@@ -449,13 +464,11 @@ extern "C" int ipk_mhsa_residual_set(ipk_relpos_attn_t* h, const ipk_mhsa_residu
     return fail(IPK_ERR_INVALID_ARG, "m_z=%d, m_y=%d must be in [0, 2^23)", r->m_z, r->m_y);
   if (!shift_ok(r->shift_r)) return fail(IPK_ERR_INVALID_ARG, "shift_r=%d outside [1, 40]", r->shift_r);
   const int d = h->d;
-  std::vector<int64_t> cb(d);
   for (int k = 0; k < d; ++k) {
     if (r->ln_mult[k] <= -(1 << 24) || r->ln_mult[k] >= (1 << 24))
       return fail(IPK_ERR_INVALID_ARG, "ln_mult[%d]=%d outside (-2^24, 2^24)", k, r->ln_mult[k]);
     if (r->ln_bias[k] <= -((int64_t)1 << 56) || r->ln_bias[k] >= ((int64_t)1 << 56))
       return fail(IPK_ERR_INVALID_ARG, "ln_bias[%d] outside (-2^56, 2^56)", k);
-    cb[k] = r->ln_bias[k] + ((int64_t)1 << (r->ln_shift - 1));
   }
   int cur = -1;
   if (hipGetDevice(&cur) != hipSuccess || cur != h->device)
@@ -482,8 +495,7 @@ extern "C" int ipk_mhsa_residual_set(ipk_relpos_attn_t* h, const ipk_mhsa_residu
   }
   // stream-ordered after every run already enqueued on the handle's device
   chk(hipDeviceSynchronize());
-  chk(hipMemcpy((void*)h->res.ln_mult, r->ln_mult, d * sizeof(int32_t), hipMemcpyHostToDevice));
-  chk(hipMemcpy((void*)h->res.ln_bias, cb.data(), d * sizeof(int64_t), hipMemcpyHostToDevice));
+  chk(upload_ln((int32_t*)h->res.ln_mult, (int64_t*)h->res.ln_bias, r->ln_mult, r->ln_bias, r->ln_shift, d));
   chk(hipDeviceSynchronize());
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -703,10 +715,7 @@ extern "C" int ipk_ffn_create(const ipk_ffn_desc* desc, ipk_ffn_t** out) {
   chk(pack_weight_fragments(stage, h->w2, (int)d, (int)f, nullptr));
   chk(upload_requant(h, &h->rq1, &desc->mult1, &desc->shift1, 1, (int)f));
   chk(upload_requant(h, &h->rq2, &desc->mult2, &desc->shift2, 1, (int)d));
-  std::vector<int64_t> cb(d);
-  for (size_t k = 0; k < d; ++k) cb[k] = desc->ln_bias[k] + ((int64_t)1 << (desc->ln_shift - 1));
-  chk(hipMemcpy(g, desc->ln_mult, d * sizeof(int32_t), hipMemcpyHostToDevice));
-  chk(hipMemcpy(c, cb.data(), d * sizeof(int64_t), hipMemcpyHostToDevice));
+  chk(upload_ln(g, c, desc->ln_mult, desc->ln_bias, desc->ln_shift, (int)d));
   chk(launch_swish_table(h->swtab, desc->sw_qc, desc->sw_q1, desc->m_sw, desc->shift_sw, nullptr));
   chk(hipDeviceSynchronize());
   if (e != hipSuccess) {
@@ -915,10 +924,7 @@ extern "C" int ipk_conv_create(const ipk_conv_desc* desc, ipk_conv_t** out) {
   chk(upload_requant(h, &h->rq_pw2, &desc->mult_pw2, &desc->shift_pw2, 1, (int)d));
   chk(hipMemcpy(bias, desc->bias_dw, d * sizeof(int32_t), hipMemcpyHostToDevice));
   chk(hipMemcpy(mdw, desc->mult_dw, d * sizeof(int32_t), hipMemcpyHostToDevice));
-  std::vector<int64_t> cb(d);
-  for (size_t k = 0; k < d; ++k) cb[k] = desc->ln_bias[k] + ((int64_t)1 << (desc->ln_shift - 1));
-  chk(hipMemcpy(g, desc->ln_mult, d * sizeof(int32_t), hipMemcpyHostToDevice));
-  chk(hipMemcpy(c, cb.data(), d * sizeof(int64_t), hipMemcpyHostToDevice));
+  chk(upload_ln(g, c, desc->ln_mult, desc->ln_bias, desc->ln_shift, (int)d));
   chk(launch_swish16_table(sw16, desc->sw_qc, desc->sw_q1, desc->m_sw, desc->shift_sw, nullptr));
   chk(launch_glu_table(glu, desc->glu_qc, desc->glu_q1, desc->m_glu, desc->shift_glu, nullptr));
   chk(hipDeviceSynchronize());
@@ -1045,13 +1051,11 @@ extern "C" int ipk_layernorm_create(const ipk_layernorm_desc* desc, ipk_layernor
   if (d < 16 || d % 16 || d > 16384) return fail(IPK_ERR_INVALID_ARG, "d_model=%d must be a multiple of 16 in [16, 16384]", d);
   if (!desc->ln_mult || !desc->ln_bias) return fail(IPK_ERR_INVALID_ARG, "ln_mult and ln_bias must be non-NULL");
   if (desc->ln_shift < 1 || desc->ln_shift > 62) return fail(IPK_ERR_INVALID_ARG, "ln_shift=%d outside [1, 62]", desc->ln_shift);
-  std::vector<int64_t> cb(d);
   for (int k = 0; k < d; ++k) {
     if (desc->ln_mult[k] <= -(1 << 24) || desc->ln_mult[k] >= (1 << 24))
       return fail(IPK_ERR_INVALID_ARG, "ln_mult[%d]=%d outside (-2^24, 2^24)", k, desc->ln_mult[k]);
     if (desc->ln_bias[k] <= -((int64_t)1 << 56) || desc->ln_bias[k] >= ((int64_t)1 << 56))
       return fail(IPK_ERR_INVALID_ARG, "ln_bias[%d] outside (-2^56, 2^56)", k);
-    cb[k] = desc->ln_bias[k] + ((int64_t)1 << (desc->ln_shift - 1));
   }
   ipk_layernorm* h = new (std::nothrow) ipk_layernorm();
   if (!h) return fail(IPK_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -1062,8 +1066,7 @@ extern "C" int ipk_layernorm_create(const ipk_layernorm_desc* desc, ipk_layernor
   if (e == hipSuccess) h->allocs.push_back(g);
   if (e == hipSuccess) e = hipMalloc(&c, d * sizeof(int64_t));
   if (e == hipSuccess) h->allocs.push_back(c);
-  if (e == hipSuccess) e = hipMemcpy(g, desc->ln_mult, d * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(c, cb.data(), d * sizeof(int64_t), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = upload_ln((int32_t*)g, (int64_t*)c, desc->ln_mult, desc->ln_bias, desc->ln_shift, d);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_ln(h);

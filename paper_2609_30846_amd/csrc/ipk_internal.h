@@ -69,8 +69,11 @@ struct Workspace {
 
 // LayerNorm and residual constants of the MHSA module (Eq. 2) on the device.
 struct Residual {
+  // in the kernel's load order, 16-channel piece p = k / 16 innermost: channel k's multiplier at
+  // ((k % 16 / 4) d/16 + p) 4 + k % 4, its bias (ln_bias + 2^(ln_shift - 1), the rounding term
+  // folded in) at ((k % 16 / 2) d/16 + p) 2 + k % 2
   const int32_t* ln_mult;  // [d]
-  const int64_t* ln_bias;  // [d]: ln_bias + 2^(ln_shift - 1), the rounding term folded in
+  const int64_t* ln_bias;  // [d]
   int32_t ln_shift;
   int32_t m_z, m_y, shift_r;
 };
