@@ -629,7 +629,11 @@ static hipError_t launch_best(int K, int min_tm, Count tiles_of, Fill fill, hipS
   for (int i = 0; i < 6; ++i) {
     const TileShape& s = kTiles[i];
     if (s.tm < min_tm) continue;
-    const double t = (double)((tiles_of(s.tn, s.tm) + kGemmCUs - 1) / kGemmCUs) * (s.fixed[EPI] + s.per_k * K / 1024.0);
+    const long rounds = (tiles_of(s.tn, s.tm) + kGemmCUs - 1) / kGemmCUs;
+    // one 256 x 256 workgroup fills a CU: with more than one round its first fetch and
+    // epilogue are uncovered (23000 tokens x 1024 -> 4096, six rounds: 120 us against 106 us)
+    if (s.tm == 256 && rounds > 1) continue;
+    const double t = (double)rounds * (s.fixed[EPI] + s.per_k * K / 1024.0);
     if (best < 0 || t < best_t) {
       best = i;
       best_t = t;
