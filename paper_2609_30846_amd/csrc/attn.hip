@@ -923,9 +923,7 @@ AttnPlan attn_plan(int DK, int T_al, long bh_count, int T) {
   return best;
 }
 
-// Raises a kernel's dynamic-LDS ceiling to the whole budget, once per device (per
-// launch the call would cost host time on every run).
-static hipError_t allow_full_lds(const void* kernel) {
+hipError_t allow_lds(const void* kernel, int bytes) {
   static std::mutex mu;
   static std::vector<std::pair<const void*, int>> done;
   int dev = 0;
@@ -934,7 +932,7 @@ static hipError_t allow_full_lds(const void* kernel) {
   std::lock_guard<std::mutex> lock(mu);
   for (const auto& d : done)
     if (d.first == kernel && d.second == dev) return hipSuccess;
-  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBudget);
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e == hipSuccess) done.emplace_back(kernel, dev);
   return e;
 }
@@ -947,7 +945,7 @@ static hipError_t launch_attn_plan(const AttnArgs& args, const AttnPlan& p, int 
     const size_t s2 = attn_lds_bytes(DK, KS2, NTL2, T_al);
     shmem = s2 > shmem ? s2 : shmem;
   }
-  hipError_t e = allow_full_lds((const void*)relpos_attn_core<DK, KS1, NTL1, KS2, NTL2, WIDE>);
+  hipError_t e = allow_lds((const void*)relpos_attn_core<DK, KS1, NTL1, KS2, NTL2, WIDE>, (int)kLdsBudget);
   if (e != hipSuccess) return e;
   AttnArgs a2 = args;
   a2.nqb = p.nqb1;

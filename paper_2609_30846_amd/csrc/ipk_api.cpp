@@ -890,14 +890,15 @@ extern "C" int ipk_conv_create(const ipk_conv_desc* desc, ipk_conv_t** out) {
   auto chk = [&](hipError_t r) {
     if (e == hipSuccess) e = r;
   };
-  int8_t *wdw = nullptr, *stage = nullptr;
-  int32_t *bias = nullptr, *mdw = nullptr, *g = nullptr;
+  int8_t* stage = nullptr;
+  int32_t *wdw = nullptr, *bias = nullptr, *mdw = nullptr, *lim = nullptr, *g = nullptr;
   int64_t* c = nullptr;
   chk(dev_alloc(h, &h->w_pw1, 2 * d * d));
   chk(dev_alloc(h, &h->w_pw2, d * d));
-  chk(dev_alloc(h, &wdw, d * 9));
+  chk(dev_alloc(h, &wdw, d * 3));
   chk(dev_alloc(h, &bias, d));
   chk(dev_alloc(h, &mdw, d));
+  chk(dev_alloc(h, &lim, d));
   chk(dev_alloc(h, &g, d));
   chk(dev_alloc(h, &c, d));
   chk(dev_alloc(h, &h->x, R * d));
@@ -905,9 +906,8 @@ extern "C" int ipk_conv_create(const ipk_conv_desc* desc, ipk_conv_t** out) {
   chk(dev_alloc(h, &h->o, R * d));
   chk(dev_alloc(h, &h->v, R * d));
   chk(dev_alloc(h, &stage, 2 * d * d));
-  int8_t* sw16 = nullptr;
-  chk(dev_alloc(h, &sw16, 65535));
-  int8_t* glu = nullptr;
+  uint8_t *sw16 = nullptr, *glu = nullptr;
+  chk(dev_alloc(h, &sw16, 65536));
   chk(dev_alloc(h, &glu, 65536));
   if (e != hipSuccess) {
     free_conv(h);
@@ -919,7 +919,21 @@ extern "C" int ipk_conv_create(const ipk_conv_desc* desc, ipk_conv_t** out) {
   chk(pack_weight_fragments(stage, h->w_pw1, 2 * (int)d, (int)d, nullptr));
   chk(hipMemcpy(stage, desc->w_pw2, d * d, hipMemcpyDefault));
   chk(pack_weight_fragments(stage, h->w_pw2, (int)d, (int)d, nullptr));
-  chk(hipMemcpy(wdw, desc->w_dw, d * 9, hipMemcpyDefault));
+  {
+    // the taps in rows of 12 bytes, and each channel's accumulator bound: for |acc| >= lim,
+    // acc m / 2^n is at least 32767 in magnitude, so RS and the clamp give +-32767
+    std::vector<int8_t> taps(d * 9), rows(d * 12, 0);
+    std::vector<int32_t> bound(d);
+    chk(hipMemcpy(taps.data(), desc->w_dw, d * 9, hipMemcpyDefault));
+    for (size_t k = 0; k < d; ++k) {
+      memcpy(&rows[k * 12], &taps[k * 9], 9);
+      const int64_t m = desc->mult_dw[k], top = (int64_t)32767 << desc->shift_dw;
+      const int64_t b = m ? (top + m - 1) / m : INT32_MAX;
+      bound[k] = (int32_t)(b < INT32_MAX ? b : INT32_MAX);
+    }
+    chk(hipMemcpy(wdw, rows.data(), d * 12, hipMemcpyHostToDevice));
+    chk(hipMemcpy(lim, bound.data(), d * sizeof(int32_t), hipMemcpyHostToDevice));
+  }
   chk(upload_requant(h, &h->rq_pw1, &desc->mult_pw1, &desc->shift_pw1, 1, 2 * (int)d));
   chk(upload_requant(h, &h->rq_pw2, &desc->mult_pw2, &desc->shift_pw2, 1, (int)d));
   chk(hipMemcpy(bias, desc->bias_dw, d * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -938,11 +952,8 @@ extern "C" int ipk_conv_create(const ipk_conv_desc* desc, ipk_conv_t** out) {
   h->mid.w_dw = wdw;
   h->mid.bias_dw = bias;
   h->mid.mult_dw = mdw;
+  h->mid.lim_dw = lim;
   h->mid.shift_dw = desc->shift_dw;
-  h->mid.glu_qc = desc->glu_qc;
-  h->mid.glu_q1 = desc->glu_q1;
-  h->mid.m_glu = desc->m_glu;
-  h->mid.shift_glu = desc->shift_glu;
   h->mid.swtab16 = sw16;
   h->mid.glutab = glu;
   h->res.ln_mult = g;

@@ -188,17 +188,16 @@ hipError_t launch_linear_resid(const int8_t* x, int rows, int N, int K, const in
 // The middle of the convolution module (Eq. 5): GLU, depthwise convolution with folded
 // BatchNorm to the INT16 grid, Swish, requantization to PW2's int8 input.
 struct ConvMiddle {
-  const int8_t* w_dw;     // [d][9]
+  const int32_t* w_dw;     // [d][3]: a channel's nine int8 taps in 12 bytes (the last three zero)
   const int32_t* bias_dw;  // [d]
   const int32_t* mult_dw;  // [d]
+  const int32_t* lim_dw;   // [d]: ceil(32767 2^shift_dw / mult): from there on the result saturates
   int shift_dw;
-  long long glu_qc, glu_q1, m_glu;
-  int shift_glu;
-  const int8_t* swtab16;  // [65535] Swish output of each int16 value v, at v + 32767
-  const int8_t* glutab;   // [256][256] GLU output of each int8 pair (a, b), at (a + 128) 256 + b + 128
+  const uint8_t* swtab16;  // [65536] Swish output of each int16 value v, at (uint16) v
+  const uint8_t* glutab;   // [256][256] GLU output of each int8 pair (a, b), at (uint8) a 256 + (uint8) b
 };
-hipError_t launch_swish16_table(int8_t* tab, long long q_c, long long q_1, long long m, int shift, hipStream_t st);
-hipError_t launch_glu_table(int8_t* tab, long long q_c, long long q_1, long long m, int shift, hipStream_t st);
+hipError_t launch_swish16_table(uint8_t* tab, long long q_c, long long q_1, long long m, int shift, hipStream_t st);
+hipError_t launch_glu_table(uint8_t* tab, long long q_c, long long q_1, long long m, int shift, hipStream_t st);
 hipError_t launch_conv_middle(const ConvMiddle& m, const int8_t* u, const Lengths& lens, int B, int T, int d,
                               int8_t* o, int16_t* v, hipStream_t st);
 hipError_t launch_layernorm_rows(long rows, int d, const Residual& r, const int8_t* z, int8_t* out, hipStream_t st);
@@ -216,6 +215,10 @@ struct AttnPlan {
   int nqb2;
 };
 AttnPlan attn_plan(int DK, int T_al, long bh_count, int T);
+
+// Raises a kernel's dynamic-LDS ceiling to `bytes`, once per device (per launch the call would
+// cost host time on every run).
+hipError_t allow_lds(const void* kernel, int bytes);
 
 // Rearranges a row-major int8 matrix [N][K] into fragment order (wfrag_index).
 hipError_t pack_weight_fragments(const int8_t* w, int8_t* dst, int N, int K, hipStream_t st);
