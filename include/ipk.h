@@ -54,8 +54,9 @@ typedef enum ipk_status {
  * Block descriptor, read only during ipk_relpos_attn_create.
  *
  * Shapes: d_model = n_heads * d_k, d_k in {64, 128}; max_batch in [1, IPK_MAX_BATCH]
- * and max_T in [1, IPK_MAX_T] size the handle's workspace.  The attention core keeps a
- * workgroup's score rows on chip, which limits max_T to 8000 (IPK_ERR_UNSUPPORTED above).
+ * and max_T in [1, IPK_MAX_T] size the handle's workspace.  The attention core takes
+ * max_T up to 8000 (IPK_ERR_UNSUPPORTED above); past 3968 frames the score rows that do not
+ * fit on chip go through a buffer of the handle (up to 33 MB, allocated at create).
  *
  * Weights (DEVICE pointers, int8, [d_out = d_model][d_in = d_model], row-major,
  * nn.Linear convention y = x W^T): w_q, w_k, w_v (the three projections of
@@ -136,7 +137,8 @@ int ipk_relpos_attn_run(ipk_relpos_attn_t* h, const int8_t* x, const int8_t* pos
  * lives in one static device array of IPK_NOALLOC_SCRATCH_BYTES per GPU instead of
  * the handle's: the library's code object holds it, each GPU the library
  * runs on keeps its copy until the process ends, and its address is looked up on the
- * device's first call.  The call allocates nothing and calls no allocating routine.
+ * device's first call.  The call allocates nothing and calls no allocating routine (past 3968
+ * frames the score rows that do not fit on chip use the handle's buffer of create).
  * Workspace bytes, each part rounded up to 256:
  *   3 B H T_al d_k + H (2 T_al + 256) d_k (only with a pos_table) + B T d_model,
  *   T_al = T rounded up to 64

@@ -40,7 +40,11 @@
 // summed from the V fragments themselves (v_dot4 against ones).  The key parts' int32
 // partial contexts are added in LDS (exact, order-free) and requantized with
 // (m_o, shift_o) in 64-bit integers.
+// Long utterances (SPILL): the keys are taken in parts whose score rows fit LDS; all but the
+// last part's scores are copied to a buffer in memory, summed from there in phase 2, and
+// converted back into LDS part by part for phase 3.
 // No floating-point instruction runs in the kernel.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <utility>
@@ -75,6 +79,11 @@ struct AttnArgs {
   int32_t m_c, m_p, shift_s;
   int64_t bias64;
   int32_t m_o, shift_o;
+  // spilling workgroups: blocks of the launch, 64-key chunks that fit LDS, and each
+  // workgroup's buffer for the others
+  int nblocks, part_chunks;
+  uint8_t* spill;
+  uint32_t spill_stride;
 };
 
 // Maximum over the 16 lanes of each row (DPP quad_perm [1,0,3,2], quad_perm [2,3,0,1],
@@ -162,7 +171,7 @@ __device__ __forceinline__ void split_pairs(int n, int older, int hk, int part, 
 
 // One workgroup of the core: block `lin` of a segment of nqb query blocks per
 // (utterance, head) that starts at query q_base.
-template <int DK, int KSPLIT, int NTL, bool WIDE>
+template <int DK, int KSPLIT, int NTL, bool WIDE, bool SPILL = false>
 __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* smem, const int lin, const DivU& dnqb,
                                            const int q_base) {
   const int nqb = (int)dnqb.d;
@@ -178,7 +187,11 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
   static_assert(NTILES <= 4, "the code tables hold four 16-row tiles");
   static_assert(KH == 2, "phase-3 wave grid");
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  // in the loop over blocks of a spilling workgroup: everything derived from the thread is
+  // computed afresh (kept across blocks it costs the registers phase 1 needs)
+  if (SPILL) asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index: uniform, kept in SGPRs
   const int col = lane & 15, g = lane >> 4;
   // Waves w and w + 4 share SIMD w % 4.  In phase 1 the two waves of a SIMD take the
@@ -216,9 +229,8 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
   if (wg_q0 >= L) {
     // no valid query in this workgroup (a ragged batch): its context rows are zeros,
     // and nothing else of it is needed
-    const int tid0 = threadIdx.x;
     constexpr int PIECES = DK / 16;  // 16-byte pieces of one row's head slice
-    for (int idx = tid0; idx < WGQ * PIECES; idx += 64 * ATTN_WAVES) {
+    for (int idx = tid; idx < WGQ * PIECES; idx += 64 * ATTN_WAVES) {
       const int qi = wg_q0 + idx / PIECES;
       if (qi < T)
         *(v4i*)(a.ctx + ((size_t)b * T + qi) * a.d + (size_t)h * DK + (idx % PIECES) * 16) = (v4i){0, 0, 0, 0};
@@ -226,8 +238,15 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
     return;
   }
   const int nkc = (L + KCHUNK - 1) / KCHUNK;
+  // SPILL: the first nsp chunks' scores go through the workgroup's buffer, in parts of at most
+  // `sp` chunks (each computed in LDS and copied out); chunks nsp .. nkc - 1 stay in LDS
+  const int nsp = SPILL ? max(0, nkc - a.part_chunks) : 0;
+  const int sp = SPILL ? (nsp > a.part_chunks ? (nsp + 1) / 2 : nsp) : 0;  // two parts reach ATTN_MAX_T
+  uint8_t* const spill = SPILL ? a.spill + (size_t)blockIdx.x * a.spill_stride : nullptr;
   int c_begin, c_end;
-  split(nkc, P2_OLDER, &c_begin, &c_end);
+  split(nkc - nsp, P2_OLDER, &c_begin, &c_end);
+  c_begin += nsp;
+  c_end += nsp;
   // chunks below c_full hold only valid keys; c_full < c_end only when this wave's
   // range holds the chunk with the utterance's last key
   const int c_full = max(c_begin, min(c_end, L / KCHUNK));
@@ -235,7 +254,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
 
   constexpr AttnLds lay0 = attn_lds(WGQ, ROWS, 0);
   const uint32_t base = (uint32_t)(uintptr_t)(lds8*)smem;
-  const uint32_t s_bytes = (uint32_t)WGQ * (uint32_t)T_al;
+  const uint32_t s_bytes = (uint32_t)WGQ * (uint32_t)(SPILL ? a.part_chunks * KCHUNK : T_al);
   const uint32_t TAB = base + s_bytes;                  // [d][32 banks] dwords
   const uint32_t ETAB = TAB + (lay0.etab - lay0.tab);   // the 256 exp values, once
   lds32* tab = (lds32*)(uintptr_t)TAB;
@@ -277,13 +296,16 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
 #pragma unroll
     for (int i = 0; i < 4; ++i) mx[t][i] = LOCODE;
 
-  // phase 1 splits the 16-key steps that hold a valid key over the key parts
-  const int nst = (L + 15) >> 4;
+  // phase 1 over keys k_first (a multiple of 64) .. k_end - 1, whose scores start at the
+  // beginning of the LDS rows
+  auto phase1 = [&](const int k_first, const int k_end) {
+  // the 16-key steps that hold a valid key are split over the key parts
+  const int nst = (k_end - k_first + 15) >> 4;
   int j_begin, j_stop;
   split(nst, P1_OLDER, &j_begin, &j_stop);
-  j_begin *= 16;
-  j_stop *= 16;
-  const int j_full = max(j_begin, min(j_stop, L & ~15));  // steps below this are unmasked
+  j_begin = k_first + 16 * j_begin;
+  j_stop = k_first + 16 * j_stop;
+  const int j_full = max(j_begin, min(j_stop, k_end & ~15));  // steps below this are unmasked
   if (active && j_begin < j_stop) {
     const uint32_t frag = (uint32_t)frag_off;
     v4i qf[NTL][NKS];
@@ -337,9 +359,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
       return r;
     };
 
-    // Register rings over the step phase S = (step index) % RING, all indices static
-    // (RING = NTL, and 2 for a single tile, so that the current and the next step never
-    // share a slot):
+    // Register rings over the step phase S = (step index) % RING, all indices static:
     //  pr[u]:    tile 0's hi-window P fragment of the step with phase u; at phase S
     //            tile t uses slot (S - t) mod RING (its window is tile 0's window of t
     //            steps before)
@@ -347,7 +367,8 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
     //  kr[u]:    K fragment of the step with phase u (current, next)
     //  gr[u][t]: position MFMA results (hi windows) of the step with phase u; a
     //            step's lo windows are the previous step's hi windows
-    constexpr int RING = NTL > 1 ? NTL : 2;
+    constexpr int RING = NTL;
+    static_assert(NTL > 1, "the current and the next step never share a ring slot");
     v4i pr[RING][NKS], kr[RING][NKS], gr[RING][NTL], bv[RING];
     {
       // tile t's hi window of the first step: tile 0's window 16 t rows lower
@@ -410,7 +431,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
 #pragma unroll
       for (int s = 0; s < NKS; ++s) pr[SN][s] = ldp(poff + adv, s);
       const bool key_ok = j0 + col < L;
-      lds8* sp = (lds8*)(uintptr_t)(sdst0 + (uint32_t)(j0 >> 4) * BLK);
+      lds8* sp = (lds8*)(uintptr_t)(sdst0 + (uint32_t)((j0 - k_first) >> 4) * BLK);
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
 #pragma unroll
@@ -456,6 +477,21 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
       if (j0 < j_stop) step(Phase<2 % RING>{}, j0 + 16 > j_full);
     }
   }
+  };
+  if constexpr (SPILL) {
+    for (int c = 0;; c += sp) {
+      const bool resident = c >= nsp;
+      const int n = resident ? nkc - nsp : min(sp, nsp - c);
+      phase1((resident ? nsp : c) * KCHUNK, resident ? L : (c + n) * KCHUNK);
+      if (resident) break;
+      __syncthreads();
+      for (int off = tid * 16; off < n * 4 * BLK; off += 16 * 64 * ATTN_WAVES)
+        __builtin_nontemporal_store(*(const ldsv4*)(uintptr_t)(base + (uint32_t)off), (v4i*)(spill + (size_t)c * (4 * BLK) + off));
+      __syncthreads();
+    }
+  } else {
+    phase1(0, L);
+  }
   // row max over the 16 key lanes of each row group
 #pragma unroll
   for (int t = 0; t < NTL; ++t)
@@ -488,7 +524,9 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
     const int nv = L - (c * KCHUNK + g * 16 + 4 * wd);  // valid keys from this dword's first
     return nv >= 4 ? dw : (nv <= 0 ? 0xffffffffu : dw | (0xffffffffu << (8 * nv)));
   };
-  auto chunk_ptr = [&](int c, int t) { return (ldsv4*)(uintptr_t)(rd0 + (uint32_t)c * (4 * BLK) + t * 256); };
+  auto chunk_ptr = [&](int c, int t) { return (ldsv4*)(uintptr_t)(rd0 + (uint32_t)(c - nsp) * (4 * BLK) + t * 256); };
+  // the same bytes of a spilled chunk
+  const uint8_t* const spill_rd = SPILL ? spill + g * BLK + (ROWS * qset + col) * 16 : nullptr;
 
   // ---------------- phase 2: row sums of the integer exp
   // lane l reads copy l % 32 of the exp table: e(d) at TAB + 4 (l % 32) + 128 d
@@ -547,6 +585,43 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
         sum[t] += acc_e;
       }
     }
+    if constexpr (SPILL) {
+      // the spilled chunks (all of them full), two in flight ahead of the two summed
+      int s_begin, s_end;
+      split(nsp, P2_OLDER, &s_begin, &s_end);
+      v4i nx[2][NTL];
+      auto ld2 = [&](int c) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < NTL; ++t)
+            nx[i][t] = __builtin_nontemporal_load((const v4i*)(spill_rd + (size_t)min(c + i, s_end - 1) * (4 * BLK) + t * 256));
+      };
+      if (s_begin < s_end) ld2(s_begin);
+      for (int c = s_begin; c < s_end; c += 2) {
+        v4i sv[2][NTL];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < NTL; ++t) sv[i][t] = nx[i][t];
+        ld2(min(c + 2, s_end - 1));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (c + i >= s_end) break;
+#pragma unroll
+          for (int t = 0; t < NTL; ++t) {
+            uint32_t acc_e = 0;
+#pragma unroll
+            for (int wd = 0; wd < 4; ++wd) {
+              const uint32_t dw = Mrep[t] - (uint32_t)sv[i][t][wd];
+#pragma unroll
+              for (int k = 0; k < 4; ++k) acc_e += e_at(dw, k);
+            }
+            sum[t] += acc_e;
+          }
+        }
+      }
+    }
   }
 #pragma unroll
   for (int t = 0; t < NTL; ++t) sum[t] = col4_sum(sum[t]);
@@ -595,20 +670,20 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
   // ---------------- conversion: every score byte of this wave's units replaced by its
   // softmax code a - 128 (lanes g = 0, 1 (and 2, 3) read the two bank copies of their
   // row, so one lookup touches 32 distinct banks)
-  if (active) {
-    uint32_t cbase[NTL];
+  uint32_t cbase[NTL];
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) cbase[t] = TAB + (uint32_t)((col + 16 * (g & 1)) * 4 + qset * NTL + t);
-    auto code_at = [&](uint32_t dw, int k, int t) {
-      return (uint32_t) * (const lds8*)(uintptr_t)__builtin_amdgcn_udot4(dw, 128u << (8 * k), cbase[t], false);
-    };
-    // four codes of one dword: two 16-bit halves (a shift-or each), then one byte
-    // permute that takes bytes 0, 1 of each (three instructions per four codes)
-    auto codes4 = [&](uint32_t dw, int t) {
-      const uint32_t lo = code_at(dw, 0, t) | (code_at(dw, 1, t) << 8);
-      const uint32_t hi = code_at(dw, 2, t) | (code_at(dw, 3, t) << 8);
-      return (int)__builtin_amdgcn_perm(hi, lo, 0x05040100u);
-    };
+  for (int t = 0; t < NTL; ++t) cbase[t] = TAB + (uint32_t)((col + 16 * (g & 1)) * 4 + qset * NTL + t);
+  auto code_at = [&](uint32_t dw, int k, int t) {
+    return (uint32_t) * (const lds8*)(uintptr_t)__builtin_amdgcn_udot4(dw, 128u << (8 * k), cbase[t], false);
+  };
+  // four codes of one dword: two 16-bit halves (a shift-or each), then one byte
+  // permute that takes bytes 0, 1 of each (three instructions per four codes)
+  auto codes4 = [&](uint32_t dw, int t) {
+    const uint32_t lo = code_at(dw, 0, t) | (code_at(dw, 1, t) << 8);
+    const uint32_t hi = code_at(dw, 2, t) | (code_at(dw, 3, t) << 8);
+    return (int)__builtin_amdgcn_perm(hi, lo, 0x05040100u);
+  };
+  if (active) {
     // the next chunk is read before the current one is written back (chunks are disjoint)
     v4i svn[NTL];
     if (c_begin < c_full) {
@@ -647,15 +722,21 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
 
   // ---------------- phase 3: A.V on MFMA, the waves split channels and keys
   const int cg = w % NCG, kh = w / NCG;
-  int a_begin, a_end;
-  split_pairs(nkc, P3_OLDER, 1, kh, &a_begin, &a_end);
   v4i acc[NTILES][AV_NT];
+  int vpart[AV_NT];  // this lane's sum of V over the keys taken
 #pragma unroll
   for (int tt = 0; tt < NTILES; ++tt)
 #pragma unroll
     for (int j = 0; j < AV_NT; ++j) acc[tt][j] = (v4i){0, 0, 0, 0};
-  const bool wg_active = wg_q0 < L;
-  if (wg_active && a_begin < a_end) {
+#pragma unroll
+  for (int j = 0; j < AV_NT; ++j) vpart[j] = 0;
+  // chunks c_first .. c_stop - 1, whose codes start at the beginning of the LDS rows
+  auto av_chunks = [&](const int c_first, const int c_stop) {
+    int a_begin, a_end;
+    split_pairs(c_stop - c_first, P3_OLDER, 1, kh, &a_begin, &a_end);
+    a_begin += c_first;
+    a_end += c_first;
+    if (a_begin >= a_end) return;
     // V^T fragment of 16 channels x 64 keys (A operand: lane (ch, g) holds keys
     // 16 g .. 16 g + 15 of channel ch); codes of 16 queries x the same keys (B operand:
     // lane (q, g) holds keys 16 g .. of row q), straight from the score blocks
@@ -664,19 +745,16 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
     const uint32_t av0 = base + (uint32_t)(g * BLK + col * 16);
     // rings over the chunk phase (chunk - a_begin) % 3, all indices static: V fragments
     // two chunks ahead, codes one chunk ahead (past the last chunk the reads re-read it)
-    int vpart[AV_NT];
     v4i vr[3][AV_NT], br[3][NTILES];
     auto ldv = [&](int c, v4i* dst) {
 #pragma unroll
       for (int j = 0; j < AV_NT; ++j) dst[j] = *(const v4i*)(vsrc + (size_t)c * CH + j * 1024);
     };
     auto ldc = [&](int c, v4i* dst) {
-      const uint32_t cp = av0 + (uint32_t)c * (4 * BLK);
+      const uint32_t cp = av0 + (uint32_t)(c - c_first) * (4 * BLK);
 #pragma unroll
       for (int tt = 0; tt < NTILES; ++tt) dst[tt] = *(const ldsv4*)(uintptr_t)(cp + tt * 256);
     };
-#pragma unroll
-    for (int j = 0; j < AV_NT; ++j) vpart[j] = 0;
     const int c_last = a_end - 1;
     ldv(a_begin, vr[0]);
     ldv(min(a_begin + 1, c_last), vr[1]);
@@ -703,6 +781,39 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
     }
     if (c < a_end) avstep(Phase<0>{});
     if (c < a_end) avstep(Phase<1>{});
+  };
+  av_chunks(nsp, nkc);
+  if constexpr (SPILL) {
+    // the spilled parts: scores from the buffer, converted into LDS, then their A.V
+    for (int c0 = 0; c0 < nsp; c0 += sp) {
+      const int n = min(sp, nsp - c0);
+      __syncthreads();
+      int s_begin, s_end;
+      split(n, P2_OLDER, &s_begin, &s_end);
+      for (int c = s_begin; c < s_end; c += 2) {
+        v4i sv[2][NTL];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < NTL; ++t)
+            sv[i][t] = __builtin_nontemporal_load((const v4i*)(spill_rd + (size_t)(c0 + min(c + i, s_end - 1)) * (4 * BLK) + t * 256));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (c + i >= s_end) break;
+#pragma unroll
+          for (int t = 0; t < NTL; ++t) {
+            v4i out;
+#pragma unroll
+            for (int wd = 0; wd < 4; ++wd) out[wd] = codes4(Mrep[t] - (uint32_t)sv[i][t][wd], t);
+            *(ldsv4*)(uintptr_t)(rd0 + (uint32_t)(c + i) * (4 * BLK) + t * 256) = out;
+          }
+        }
+      }
+      __syncthreads();
+      av_chunks(c0, c0 + n);
+    }
+  }
+  {
     // exact correction for the -128 offset: + 128 * sum of V over the same keys.  Lane
     // (ch, g) summed keys 16 g .. of channel ch; the output lane (q, g) needs channels
     // 4 g .. 4 g + 3.
@@ -775,6 +886,24 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void relpos_attn_core(AttnArgs a) 
   }
 }
 
+// Long utterances, whose score rows do not fit LDS: workgroups of 16 NTL queries (eight key
+// splits) that pass the scores of the keys beyond LDS through a buffer of their own.  One
+// workgroup per CU walks over the blocks, so the buffers are 256 at most.
+template <int DK, int NTL, bool WIDE>
+__global__ __launch_bounds__(64 * ATTN_WAVES) void relpos_attn_spill(AttnArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nblocks = a.nblocks;
+  for (int lin = blockIdx.x; lin < nblocks; lin += gridDim.x) {
+    // the arguments are read from the kernel's argument block for each block: held in
+    // scalar registers over the loop they spilled
+    auto kp = (const __attribute__((address_space(4))) AttnArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kp));
+    const AttnArgs& ar = *(const AttnArgs*)kp;
+    attn_block<DK, ATTN_WAVES, NTL, WIDE, true>(ar, smem, lin, ar.dv_nqb, 0);
+    __syncthreads();  // the next block's tables and scores overwrite this one's
+  }
+}
+
 // The I-BERT integer exp of every score distance d = M - s in [0, 254] (Sec. 2.2:
 // d = z q_ln2 - r with r in (-q_ln2, 0], e = ((r + q_b)^2 + q_c) >> z), and 0 at d = 255,
 // which no score reaches; integer arithmetic only.  One thread per d.
@@ -838,14 +967,30 @@ size_t attn_lds_bytes(int DK, int ksplit, int ntl, int T_al) {
 
 // Workgroup shapes the kernel is built for: (key splits, 16-query tiles per wave).
 static const AttnCfg kAttnCfgs[] = {{4, 2}, {8, 2}, {8, 3}};
-// One 16-query tile per wave: the smallest score rows, for utterances whose rows do not
-// fit any shape above (every K and P fragment then feeds a single MFMA)
-static const AttnCfg kAttnLong = {8, 1};
+// Utterances whose score rows fit no shape above (past 3968 frames): 32-query workgroups that
+// pass the scores of the keys beyond LDS through a buffer in memory.  Every K, P and V
+// fragment still feeds two MFMAs; 16-query workgroups, whose rows fit to 8000 frames, feed one:
+// T = 6000, 8 heads 333 us against 280 us, T = 4500 196 against 170, T = 8000, 4 heads 309
+// against 268.  48 queries would need fewer passes but spill twice the bytes per query, and the
+// compiler's schedule of their loop ran at 323 us.
+static const AttnCfg kAttnSpill = {8, 2};
 constexpr size_t kLdsBudget = 160 * 1024;
 constexpr int kNumCUs = 256;
 
 static int wgq_of(const AttnCfg& c) { return 16 * c.ntl * (ATTN_WAVES / c.ksplit); }
 static bool fits(const AttnCfg& c, int DK, int T_al) { return attn_lds_bytes(DK, c.ksplit, c.ntl, T_al) <= kLdsBudget; }
+
+// Chunks of 64 keys whose score rows fit LDS beside a shape's tables, and the bytes of a
+// workgroup's buffer for the rest of an utterance of T_al keys.
+static int part_chunks_of(const AttnCfg& c) {
+  const int wgq = wgq_of(c);
+  return (int)((kLdsBudget - attn_lds(wgq, 16 * c.ntl, 0).total) / ((size_t)wgq * KCHUNK));
+}
+static size_t spill_stride_of(const AttnCfg& c, int T_al) {
+  const int over = T_al / KCHUNK - part_chunks_of(c);
+  return over > 0 ? (size_t)over * KCHUNK * wgq_of(c) : 0;
+}
+size_t attn_spill_bytes(int T_al) { return spill_stride_of(kAttnSpill, T_al) * kNumCUs; }
 
 // Time of one workgroup, modelled per key of a wave's share as 125 cycles for the K, P
 // and V streams (the same for any number of query tiles) plus 29 per 16-query tile
@@ -894,7 +1039,7 @@ static double makespan(const long* count, const double* cost, int ng) {
 
 // Plan of one launch: a single workgroup shape, or 48-query workgroups for whole
 // rounds followed by 32-query ones for the remaining queries, whichever finishes
-// first by the model above.  c1.ksplit == 0 if no shape fits in LDS.
+// first by the model above.  c1.ksplit == 0 if no shape fits in LDS (spilling workgroups).
 AttnPlan attn_plan(int DK, int T_al, long bh_count, int T) {
   AttnPlan best{};
   double best_t = 0.0;
@@ -909,8 +1054,6 @@ AttnPlan attn_plan(int DK, int T_al, long bh_count, int T) {
   };
   for (const AttnCfg& c : kAttnCfgs)
     if (fits(c, DK, T_al)) consider(AttnPlan{c, (T + wgq_of(c) - 1) / wgq_of(c), AttnCfg{0, 0}, 0});
-  if (best.c1.ksplit == 0 && fits(kAttnLong, DK, T_al))
-    return AttnPlan{kAttnLong, (T + wgq_of(kAttnLong) - 1) / wgq_of(kAttnLong), AttnCfg{0, 0}, 0};
   const AttnCfg c1{8, 3}, c2{8, 2};
   if (fits(c1, DK, T_al) && fits(c2, DK, T_al)) {
     const int per_round = (int)(kNumCUs / bh_count);  // blocks per (utterance, head) in one round
@@ -962,14 +1105,32 @@ static hipError_t launch_attn_plan(const AttnArgs& args, const AttnPlan& p, int 
 }
 
 template <int DK, bool WIDE>
+static hipError_t launch_attn_spill(const AttnArgs& args, const RunShape& rs, hipStream_t st, const LaunchEv& ev) {
+  constexpr int NTL = 2;
+  const AttnCfg& c = kAttnSpill;
+  const hipError_t e = allow_lds((const void*)relpos_attn_spill<DK, NTL, WIDE>, (int)kLdsBudget);
+  if (e != hipSuccess) return e;
+  AttnArgs a = args;
+  a.nqb = (rs.T + wgq_of(c) - 1) / wgq_of(c);
+  a.xcd_group = (rs.B * rs.H) % 8 == 0;
+  a.dv_nqb = make_div((uint32_t)a.nqb);
+  a.dv_H = make_div((uint32_t)rs.H);
+  a.nblocks = a.nqb * rs.B * rs.H;
+  a.part_chunks = part_chunks_of(c);
+  a.spill_stride = (uint32_t)spill_stride_of(c, rs.T_al);
+  return launch_kernel(relpos_attn_spill<DK, NTL, WIDE>, dim3(std::min(a.nblocks, kNumCUs)), dim3(64 * ATTN_WAVES),
+                       attn_lds(wgq_of(c), 16 * NTL, a.part_chunks * KCHUNK).total, st, ev, a);
+}
+
+template <int DK, bool WIDE>
 static hipError_t launch_attn_dk(const AttnArgs& a, const RunShape& rs, hipStream_t st, const LaunchEv& ev) {
   const AttnPlan p = attn_plan(DK, rs.T_al, (long)rs.B * rs.H, rs.T);
+  if (p.c1.ksplit == 0) return a.spill ? launch_attn_spill<DK, WIDE>(a, rs, st, ev) : hipErrorInvalidValue;
   auto is = [](const AttnCfg& c, int ks, int ntl) { return c.ksplit == ks && c.ntl == ntl; };
   if (p.c2.ksplit == 0) {
     if (is(p.c1, 4, 2)) return launch_attn_plan<DK, 4, 2, 0, 0, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);
     if (is(p.c1, 8, 2)) return launch_attn_plan<DK, 8, 2, 0, 0, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);
     if (is(p.c1, 8, 3)) return launch_attn_plan<DK, 8, 3, 0, 0, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);
-    if (is(p.c1, 8, 1)) return launch_attn_plan<DK, 8, 1, 0, 0, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);
   } else if (is(p.c1, 8, 3) && is(p.c2, 8, 2)) {
     return launch_attn_plan<DK, 8, 3, 8, 2, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);
   }
@@ -987,6 +1148,7 @@ hipError_t launch_attention(const RunShape& rs, const Weights& w, const Scalars&
   a.v = w.v;
   a.etab = w.etab;
   a.ctx = ws.ctx;
+  a.spill = attn_spill_bytes(rs.T_al) <= ws.spill_bytes ? ws.spill : nullptr;
   a.lens = lens;
   a.T = rs.T;
   a.T_al = rs.T_al;

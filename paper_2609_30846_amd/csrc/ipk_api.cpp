@@ -218,8 +218,8 @@ extern "C" int ipk_relpos_attn_create(const ipk_relpos_attn_desc* desc, ipk_relp
   *out = nullptr;
   int st = validate_desc(desc);
   if (st != IPK_OK) return st;
-  if (attn_plan(desc->d_k, t_aligned(desc->max_T), 1, desc->max_T).c1.ksplit == 0)
-    return fail(IPK_ERR_UNSUPPORTED, "max_T=%d does not fit the on-chip score rows", desc->max_T);
+  if (desc->max_T > ATTN_MAX_T)
+    return fail(IPK_ERR_UNSUPPORTED, "max_T=%d does not fit the on-chip score rows (%d frames)", desc->max_T, ATTN_MAX_T);
 
   ipk_relpos_attn* h = new (std::nothrow) ipk_relpos_attn();
   if (!h) return fail(IPK_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -270,6 +270,8 @@ extern "C" int ipk_relpos_attn_create(const ipk_relpos_attn_desc* desc, ipk_relp
   chk(dev_alloc(h, &h->ws.vt, Bm * H * DK * T_al));
   chk(dev_alloc(h, &h->ws.p, H * PR * DK));
   chk(dev_alloc(h, &h->ws.ctx, Bm * (size_t)h->max_T * d));
+  h->ws.spill_bytes = attn_spill_bytes((int)T_al);
+  if (h->ws.spill_bytes) chk(dev_alloc(h, &h->ws.spill, h->ws.spill_bytes));
   if (e != hipSuccess) {
     free_handle(h);
     (void)hipGetLastError();
@@ -440,6 +442,8 @@ extern "C" int ipk_relpos_attn_run_noalloc(ipk_relpos_attn_t* h, const int8_t* x
   const hipError_t e = noalloc_scratch(&base, &cap);
   if (e != hipSuccess) return fail(IPK_ERR_HIP, "looking up the scratch array failed: %s", hipGetErrorString(e));
   carve_workspace(rs, pos_table != nullptr, base, &ws);
+  ws.spill = h->ws.spill;  // allocated at create, like the weights
+  ws.spill_bytes = h->ws.spill_bytes;
   return enqueue_run(h, rs, lens, ws, x, pos_table, y, stream, nullptr, true);
 }
 

@@ -65,6 +65,9 @@ __host__ __device__ inline size_t vt_index(int t, int kk, int DK) {
 struct Workspace {
   int8_t *q, *k, *vt, *p, *ctx;
   int8_t* xln;  // LayerNorm output [B][T][d] of the MHSA module's runs
+  // score rows of long utterances that do not fit LDS (attn_spill_bytes); NULL: none
+  uint8_t* spill;
+  size_t spill_bytes;
 };
 
 // LayerNorm and residual constants of the MHSA module (Eq. 2) on the device.
@@ -204,7 +207,7 @@ hipError_t launch_layernorm_rows(long rows, int d, const Residual& r, const int8
 
 // Workgroup shapes of the attention core for a run: the first shape's nqb1 query
 // blocks per (utterance, head), then (c2.ksplit != 0) the second shape's nqb2 blocks
-// for the remaining queries.  c1.ksplit == 0 when T_al does not fit LDS.
+// for the remaining queries.  c1.ksplit == 0 when T_al does not fit LDS (spilling workgroups).
 struct AttnCfg {
   int ksplit, ntl;  // key splits per query set, 16-query tiles per wave
 };
@@ -215,6 +218,12 @@ struct AttnPlan {
   int nqb2;
 };
 AttnPlan attn_plan(int DK, int T_al, long bh_count, int T);
+// Longest utterance of the attention core (its spilling workgroups take the keys in three
+// parts at most).
+constexpr int ATTN_MAX_T = 8000;
+// Bytes of the attention core's spill buffers for utterances of up to T_al keys (0 when the
+// score rows fit LDS).
+size_t attn_spill_bytes(int T_al);
 
 // Raises a kernel's dynamic-LDS ceiling to `bytes`, once per device (per launch the call would
 // cost host time on every run).
