@@ -138,6 +138,8 @@ _lock = threading.Lock()
 def load():
     """Loads libipk.so (raises FileNotFoundError if it has not been built)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -176,12 +178,25 @@ def _ptr(t) -> int:
     return 0 if t is None else int(t.data_ptr())
 
 
+def _device(device):
+    """The torch device a handle lives on, with its index (the current one's if unnamed)."""
+    import torch
+
+    dev = torch.device(device)
+    return torch.device("cuda", torch.cuda.current_device()) if dev.type == "cuda" and dev.index is None else dev
+
+
 def _tensor(t, name: str, shape, device, dtype=None):
     """Raises ValueError unless ``t`` is a contiguous int8 (or ``dtype``) tensor of
     ``shape`` on ``device``: the library takes raw pointers and trusts their extents."""
     import torch
 
     dtype = torch.int8 if dtype is None else dtype
+    # one test of everything on the way of every call (``device`` with its index, ``shape`` a
+    # tuple); what is wrong is found out below
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.shape == shape and t.is_contiguous()
+            and t.device == device):
+        return t
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{name} must be a torch tensor")
     if t.dtype != dtype:
@@ -190,9 +205,7 @@ def _tensor(t, name: str, shape, device, dtype=None):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    dev = torch.device(device)
-    if dev.type == "cuda" and dev.index is None:
-        dev = torch.device("cuda", torch.cuda.current_device())
+    dev = _device(device)
     if t.device != dev:
         raise ValueError(f"{name} is on {t.device}, the handle's device is {dev}")
     return t
@@ -206,9 +219,20 @@ def _lengths(lengths, B: int, T: int):
     lens = np.asarray(lengths).reshape(-1)
     if lens.shape[0] != B:
         raise ValueError(f"lengths holds {lens.shape[0]} values for B={B}")
-    if lens.size and (lens.min() < 1 or lens.max() > T):
+    # numpy's reductions cost more than Python's over a few values
+    lo, hi = (lens.min(), lens.max()) if B > 32 else (min(lens.tolist(), default=1), max(lens.tolist(), default=T))
+    if lo < 1 or hi > T:
         raise ValueError(f"lengths must lie in [1, T={T}]")
     return lens
+
+
+def _host_lengths(lengths):
+    """(array to keep alive, address) of ``lengths`` as contiguous int32, or (None, None)."""
+    if lengths is None:
+        return None, None
+    if not (type(lengths) is np.ndarray and lengths.dtype == np.int32 and lengths.flags.c_contiguous):
+        lengths = np.ascontiguousarray(np.asarray(lengths, dtype=np.int32))
+    return lengths, lengths.__array_interface__["data"][0]
 
 
 def _stream_ptr(stream) -> Optional[int]:
@@ -227,20 +251,14 @@ def ipk_relpos_attn_create(desc: Desc) -> int:
 
 def ipk_relpos_attn_run(h: int, x, pos_table, lengths: Optional[Sequence[int]], B: int, T: int, y,
                         stream=None) -> None:
-    lens = None
-    if lengths is not None:
-        lens = np.ascontiguousarray(np.asarray(lengths, dtype=np.int32))
-    lp = lens.ctypes.data if lens is not None else None
+    lens, lp = _host_lengths(lengths)
     _check(load().ipk_relpos_attn_run(h, _ptr(x), _ptr(pos_table), lp, int(B), int(T), _ptr(y),
                                       _stream_ptr(stream)))
 
 
 def ipk_relpos_attn_run_noalloc(h: int, x, pos_table, lengths: Optional[Sequence[int]], B: int, T: int, y,
                                 stream=None) -> None:
-    lens = None
-    if lengths is not None:
-        lens = np.ascontiguousarray(np.asarray(lengths, dtype=np.int32))
-    lp = lens.ctypes.data if lens is not None else None
+    lens, lp = _host_lengths(lengths)
     _check(load().ipk_relpos_attn_run_noalloc(h, _ptr(x), _ptr(pos_table), lp, int(B), int(T), _ptr(y),
                                               _stream_ptr(stream)))
 
@@ -266,10 +284,7 @@ def ipk_mhsa_residual_set(h: int, desc: ResidualDesc) -> None:
 
 def ipk_mhsa_residual_run(h: int, z1, pos_table, lengths: Optional[Sequence[int]], B: int, T: int, z2,
                           stream=None) -> None:
-    lens = None
-    if lengths is not None:
-        lens = np.ascontiguousarray(np.asarray(lengths, dtype=np.int32))
-    lp = lens.ctypes.data if lens is not None else None
+    lens, lp = _host_lengths(lengths)
     _check(load().ipk_mhsa_residual_run(h, _ptr(z1), _ptr(pos_table), lp, int(B), int(T), _ptr(z2),
                                         _stream_ptr(stream)))
 
@@ -338,7 +353,7 @@ class RelPosAttn:
         desc.zp_y = int(consts.get("zp_y", 0))
         with torch.cuda.device(dev):
             self.handle = ipk_relpos_attn_create(desc)
-        self.device = dev
+        self.device, self._dev = dev, _device(dev)
         self.d_model, self.n_heads = d_model, n_heads
         self.max_batch, self.max_T = max_batch, max_T
 
@@ -352,11 +367,11 @@ class RelPosAttn:
         if x.dim() != 3:
             raise ValueError(f"x must be [B][T][d_model], got shape {tuple(x.shape)}")
         B, T, _ = x.shape
-        _tensor(x, "x", (B, T, self.d_model), self.device)
+        _tensor(x, "x", (B, T, self.d_model), self._dev)
         if pos_table is not None:
-            _tensor(pos_table, "pos_table", (2 * T - 1, self.d_model), self.device)
+            _tensor(pos_table, "pos_table", (2 * T - 1, self.d_model), self._dev)
         if y is not None:
-            _tensor(y, "y", (B, T, self.d_model), self.device)
+            _tensor(y, "y", (B, T, self.d_model), self._dev)
         return B, T, _lengths(lengths, B, T)
 
     def __call__(self, x, pos_table, lengths=None, y=None, stream=None):
@@ -388,7 +403,7 @@ class RelPosAttn:
         if pos_table.dim() != 2 or pos_table.shape[0] % 2 == 0:
             raise ValueError(f"pos_table must be [2 T - 1][d_model], got shape {tuple(pos_table.shape)}")
         T_table = (pos_table.shape[0] + 1) // 2
-        _tensor(pos_table, "pos_table", (2 * T_table - 1, self.d_model), self.device)
+        _tensor(pos_table, "pos_table", (2 * T_table - 1, self.d_model), self._dev)
         ipk_relpos_attn_cache_positions(self.handle, pos_table, T_table, stream)
 
     def set_residual(self, ln_mult, ln_bias, ln_shift: int, m_z: int, m_y: int, shift_r: int):
@@ -474,7 +489,7 @@ class FeedForward:
             setattr(desc, k, int(getattr(ffn, k)))
         with torch.cuda.device(dev):
             self.handle = ipk_ffn_create(desc)
-        self.device = dev
+        self.device, self._dev = dev, _device(dev)
         self.d_model, self.d_ff, self.max_rows = int(ffn.d_model), int(ffn.d_ff), int(max_rows)
 
     def __call__(self, z, z_out=None, stream=None):
@@ -483,9 +498,9 @@ class FeedForward:
         if z.numel() % self.d_model or z.shape[-1] != self.d_model:
             raise ValueError(f"z must end in d_model={self.d_model}, got shape {tuple(z.shape)}")
         rows = z.numel() // self.d_model
-        _tensor(z, "z", tuple(z.shape), self.device)
+        _tensor(z, "z", tuple(z.shape), self._dev)
         if z_out is not None:
-            _tensor(z_out, "z_out", tuple(z.shape), self.device)
+            _tensor(z_out, "z_out", tuple(z.shape), self._dev)
         if z_out is None:
             z_out = torch.empty_like(z)
         ipk_ffn_run(self.handle, z, rows, z_out, stream)
@@ -518,10 +533,7 @@ def ipk_conv_create(desc: ConvDesc) -> int:
 
 
 def ipk_conv_run(h: int, z, lengths: Optional[Sequence[int]], B: int, T: int, z_out, stream=None) -> None:
-    lens = None
-    if lengths is not None:
-        lens = np.ascontiguousarray(np.asarray(lengths, dtype=np.int32))
-    lp = lens.ctypes.data if lens is not None else None
+    lens, lp = _host_lengths(lengths)
     _check(load().ipk_conv_run(h, _ptr(z), lp, int(B), int(T), _ptr(z_out), _stream_ptr(stream)))
 
 
@@ -560,7 +572,7 @@ class ConvModule:
             setattr(desc, k, int(getattr(cv, k)))
         with torch.cuda.device(dev):
             self.handle = ipk_conv_create(desc)
-        self.device = dev
+        self.device, self._dev = dev, _device(dev)
         self.d_model = int(cv.d_model)
 
     def __call__(self, z, lengths=None, z_out=None, stream=None):
@@ -569,9 +581,9 @@ class ConvModule:
         if z.dim() != 3:
             raise ValueError(f"z must be [B][T][d_model], got shape {tuple(z.shape)}")
         B, T, _ = z.shape
-        _tensor(z, "z", (B, T, self.d_model), self.device)
+        _tensor(z, "z", (B, T, self.d_model), self._dev)
         if z_out is not None:
-            _tensor(z_out, "z_out", (B, T, self.d_model), self.device)
+            _tensor(z_out, "z_out", (B, T, self.d_model), self._dev)
         lengths = _lengths(lengths, B, T)
         if z_out is None:
             z_out = torch.empty_like(z)
@@ -626,16 +638,16 @@ class LayerNorm:
         desc = LayerNormDesc(int(d_model), g.ctypes.data, c.ctypes.data, int(p.ln_shift))
         with torch.cuda.device(dev):
             self.handle = ipk_layernorm_create(desc)
-        self.device, self.d_model = dev, int(d_model)
+        self.device, self._dev, self.d_model = dev, _device(dev), int(d_model)
 
     def __call__(self, z, x=None, stream=None):
         import torch
 
         if z.numel() % self.d_model or z.shape[-1] != self.d_model:
             raise ValueError(f"z must end in d_model={self.d_model}, got shape {tuple(z.shape)}")
-        _tensor(z, "z", tuple(z.shape), self.device)
+        _tensor(z, "z", tuple(z.shape), self._dev)
         if x is not None:
-            _tensor(x, "x", tuple(z.shape), self.device)
+            _tensor(x, "x", tuple(z.shape), self._dev)
         if x is None:
             x = torch.empty_like(z)
         ipk_layernorm_run(self.handle, z, z.numel() // self.d_model, x, stream)
