@@ -872,9 +872,10 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
 
 // The core kernel: one workgroup shape (NTL2 == 0), or two shapes in one grid, the
 // first one's blocks ahead of the second one's, so that the second shape fills what
-// the first leaves of the last round (workgroups start in block order).
-template <int DK, int KS1, int NTL1, int KS2, int NTL2, bool WIDE>
-__global__ __launch_bounds__(64 * ATTN_WAVES) void relpos_attn_core(AttnArgs a) {
+// the first leaves of the last round (workgroups start in block order).  DENSE: compiled for
+// at most 128 registers, so that two workgroups share a CU where LDS lets them.
+template <int DK, int KS1, int NTL1, int KS2, int NTL2, bool WIDE, bool DENSE = false>
+__global__ __launch_bounds__(64 * ATTN_WAVES, DENSE ? 4 : 2) void relpos_attn_core(AttnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   if constexpr (NTL2 == 0) {
     attn_block<DK, KS1, NTL1, WIDE>(a, smem, blockIdx.x, a.dv_nqb, 0);
@@ -1006,6 +1007,21 @@ static double wg_cost(const AttnCfg& c, int T) {
   return kWgFixedCost + ((double)T / c.ksplit) * (125.0 + 29.0 * c.ntl);
 }
 
+// Time of `count` workgroups, two to a CU.  A pair overlaps the fixed part of each other's
+// time (barriers, tables, first loads) and shares the rest: 1.13 times the fixed part plus 2.06
+// times the part that scales with T, from 30 x 200, 16 x 375 and 8 x 500 frames (core 35.9 ->
+// 27.0, 31.5 -> 27.6 and 27.4 -> 23.4 us).  Alone on a CU, as in a last round of at most one per
+// CU, the kernel for at most 128 registers is 8 - 16 % slower than the ordinary one (T = 1000,
+// 256 workgroups: 15.0 us against 13.8; T = 3500: 131 against 113).
+static double pairs_time(long count, const AttnCfg& c, int T) {
+  const double pair = 1.13 * kWgFixedCost + 2.06 * (wg_cost(c, T) - kWgFixedCost);
+  const long full = count / (2 * kNumCUs), rest = count % (2 * kNumCUs);
+  return full * pair + (rest > kNumCUs ? pair : rest > 0 ? 1.1 * wg_cost(c, T) : 0.0);
+}
+static bool fits_twice(const AttnCfg& c, int DK, int T_al) {
+  return c.ntl == 2 && 2 * attn_lds_bytes(DK, c.ksplit, c.ntl, T_al) <= kLdsBudget;
+}
+
 // Finishing time of groups of workgroups (count[g] of cost[g] each) started in order on
 // the CUs, one workgroup per CU (eight waves of more than 128 VGPRs), each CU taking the
 // next workgroup when it is free.  CUs are kept in buckets of equal free time.
@@ -1046,14 +1062,18 @@ AttnPlan attn_plan(int DK, int T_al, long bh_count, int T) {
   auto consider = [&](const AttnPlan& p) {
     const long cnt[2] = {bh_count * p.nqb1, bh_count * p.nqb2};
     const double cst[2] = {wg_cost(p.c1, T), p.c2.ksplit ? wg_cost(p.c2, T) : 0.0};
-    const double t = makespan(cnt, cst, p.c2.ksplit ? 2 : 1);
+    const double t = p.dense ? pairs_time(cnt[0], p.c1, T) : makespan(cnt, cst, p.c2.ksplit ? 2 : 1);
     if (best.c1.ksplit == 0 || t < best_t) {
       best = p;
       best_t = t;
     }
   };
   for (const AttnCfg& c : kAttnCfgs)
-    if (fits(c, DK, T_al)) consider(AttnPlan{c, (T + wgq_of(c) - 1) / wgq_of(c), AttnCfg{0, 0}, 0});
+    if (fits(c, DK, T_al)) {
+      const int nqb = (T + wgq_of(c) - 1) / wgq_of(c);
+      consider(AttnPlan{c, nqb, AttnCfg{0, 0}, 0});
+      if (fits_twice(c, DK, T_al) && bh_count * nqb > kNumCUs) consider(AttnPlan{c, nqb, AttnCfg{0, 0}, 0, true});
+    }
   const AttnCfg c1{8, 3}, c2{8, 2};
   if (fits(c1, DK, T_al) && fits(c2, DK, T_al)) {
     const int per_round = (int)(kNumCUs / bh_count);  // blocks per (utterance, head) in one round
@@ -1080,7 +1100,7 @@ hipError_t allow_lds(const void* kernel, int bytes) {
   return e;
 }
 
-template <int DK, int KS1, int NTL1, int KS2, int NTL2, bool WIDE>
+template <int DK, int KS1, int NTL1, int KS2, int NTL2, bool WIDE, bool DENSE = false>
 static hipError_t launch_attn_plan(const AttnArgs& args, const AttnPlan& p, int B, int H, int T_al, hipStream_t st,
                                    const LaunchEv& ev) {
   size_t shmem = attn_lds_bytes(DK, KS1, NTL1, T_al);
@@ -1088,7 +1108,8 @@ static hipError_t launch_attn_plan(const AttnArgs& args, const AttnPlan& p, int 
     const size_t s2 = attn_lds_bytes(DK, KS2, NTL2, T_al);
     shmem = s2 > shmem ? s2 : shmem;
   }
-  hipError_t e = allow_lds((const void*)relpos_attn_core<DK, KS1, NTL1, KS2, NTL2, WIDE>, (int)kLdsBudget);
+  constexpr auto kernel = relpos_attn_core<DK, KS1, NTL1, KS2, NTL2, WIDE, DENSE>;
+  hipError_t e = allow_lds((const void*)kernel, (int)kLdsBudget);
   if (e != hipSuccess) return e;
   AttnArgs a2 = args;
   a2.nqb = p.nqb1;
@@ -1100,8 +1121,7 @@ static hipError_t launch_attn_plan(const AttnArgs& args, const AttnPlan& p, int 
   a2.dv_nqb2 = make_div((uint32_t)(p.nqb2 > 0 ? p.nqb2 : 1));
   a2.dv_H = make_div((uint32_t)H);
   dim3 grid((p.nqb1 + p.nqb2) * B * H);
-  return launch_kernel(relpos_attn_core<DK, KS1, NTL1, KS2, NTL2, WIDE>, grid, dim3(64 * ATTN_WAVES),
-                       (uint32_t)shmem, st, ev, a2);
+  return launch_kernel(kernel, grid, dim3(64 * ATTN_WAVES), (uint32_t)shmem, st, ev, a2);
 }
 
 template <int DK, bool WIDE>
@@ -1127,6 +1147,10 @@ static hipError_t launch_attn_dk(const AttnArgs& a, const RunShape& rs, hipStrea
   const AttnPlan p = attn_plan(DK, rs.T_al, (long)rs.B * rs.H, rs.T);
   if (p.c1.ksplit == 0) return a.spill ? launch_attn_spill<DK, WIDE>(a, rs, st, ev) : hipErrorInvalidValue;
   auto is = [](const AttnCfg& c, int ks, int ntl) { return c.ksplit == ks && c.ntl == ntl; };
+  // with d_k = 64 the ordinary kernels need fewer than 128 registers as they are
+  constexpr bool PAIR = DK == 128;
+  if (p.dense && is(p.c1, 4, 2)) return launch_attn_plan<DK, 4, 2, 0, 0, WIDE, PAIR>(a, p, rs.B, rs.H, rs.T_al, st, ev);
+  if (p.dense && is(p.c1, 8, 2)) return launch_attn_plan<DK, 8, 2, 0, 0, WIDE, PAIR>(a, p, rs.B, rs.H, rs.T_al, st, ev);
   if (p.c2.ksplit == 0) {
     if (is(p.c1, 4, 2)) return launch_attn_plan<DK, 4, 2, 0, 0, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);
     if (is(p.c1, 8, 2)) return launch_attn_plan<DK, 8, 2, 0, 0, WIDE>(a, p, rs.B, rs.H, rs.T_al, st, ev);

@@ -216,6 +216,7 @@ struct AttnPlan {
   int nqb1;
   AttnCfg c2;
   int nqb2;
+  bool dense = false;  // two workgroups of c1 per CU
 };
 AttnPlan attn_plan(int DK, int T_al, long bh_count, int T);
 // Longest utterance of the attention core (its spilling workgroups take the keys in three
