@@ -57,6 +57,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "gemm_tiles.h"
 #include "ipk_internal.h"
 
 namespace ipk {
@@ -76,13 +77,10 @@ struct GemmProblem {
   const int32_t* req;   // [2][N] per output channel: multiplier, and shift in the wide form (Requant)
   int wide;             // 64-bit evaluation
   int clamp;            // the fast form's clamp bound
-  int nb, rows, N, K;
+  int rows, N, K;
   int mode;
-  int tile_begin;   // first logical tile of this problem
-  int tiles_n;      // tiles along N
-  int tiles_m_per;  // token tiles per utterance
-  int band;         // token tiles per band of the logical order
-  DivU dv_band_span, dv_band, dv_last_band, dv_tiles_m_per;  // divisors of the tile decomposition
+  int tile_begin;  // first logical tile of this problem
+  TileGrid grid;
 };
 
 struct GemmArgs {
@@ -252,24 +250,16 @@ __global__ __launch_bounds__(64 * NWAVE, NWAVE == 8 ? 1 : 2) void gemm_i8_requan
   const GemmProblem& P = args.prob[pi];
   // the problem's scalars, all loaded at once: left alone the compiler loads each one
   // where it is first used, and every division below would wait for its own load
-  int tile_begin = P.tile_begin, nb = P.nb, tiles_m_per = P.tiles_m_per, band = P.band, tiles_n = P.tiles_n;
-  uint32_t m_span = P.dv_band_span.m, m_band = P.dv_band.m, m_last = P.dv_last_band.m, m_tmp = P.dv_tiles_m_per.m;
-  int K = P.K, rows = P.rows, N = P.N, mode = P.mode;
+  TileGrid grid = P.grid;
+  int tile_begin = P.tile_begin, K = P.K, rows = P.rows, N = P.N, mode = P.mode;
   asm volatile(""
-               : "+s"(tile_begin), "+s"(nb), "+s"(tiles_m_per), "+s"(band), "+s"(tiles_n), "+s"(m_span), "+s"(m_band),
-                 "+s"(m_last), "+s"(m_tmp), "+s"(K), "+s"(rows), "+s"(N), "+s"(mode));
-  // logical order inside a problem: bands of `band` token tiles, channels outer,
-  // tokens inner within a band
-  const int local = tile - tile_begin;
-  const int tiles_m = nb * tiles_m_per;
-  const int band_idx = (int)div_u(local, DivU{0u, m_span});
-  const int in_band = local - band_idx * band * tiles_n;
-  const int band_m = min(band, tiles_m - band_idx * band);
-  const int nt = (int)div_u(in_band, DivU{0u, band_m == band ? m_band : m_last});
-  const int mt = band_idx * band + (in_band - nt * band_m);
-  const int n0 = nt * TN;
-  const int ub = (int)div_u(mt, DivU{0u, m_tmp});  // utterance
-  const int t0 = (mt - ub * tiles_m_per) * TM;      // first token
+               : "+s"(tile_begin), "+s"(grid.tiles_n), "+s"(grid.tiles_m), "+s"(grid.tiles_m_per), "+s"(grid.band),
+                 "+s"(grid.span.m), "+s"(grid.span.s), "+s"(grid.full.m), "+s"(grid.full.s), "+s"(grid.last.m),
+                 "+s"(grid.last.s), "+s"(grid.per.m), "+s"(grid.per.s), "+s"(K), "+s"(rows), "+s"(N), "+s"(mode));
+  const TilePos pos = tile_at(grid, tile - tile_begin);
+  const int n0 = pos.nt * TN;
+  const int ub = pos.ub;       // utterance
+  const int t0 = pos.mt * TM;  // first token
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -542,28 +532,13 @@ static int add_problem(GemmArgs& a, int idx, const int8_t* x, const int8_t* w, c
   p.req = rq.req;
   p.wide = rq.wide;
   p.clamp = rq.clamp;
-  p.nb = nb;
   p.rows = rows;
   p.N = N;
   p.K = K;
   p.mode = mode;
   p.tile_begin = tile_begin;
-  p.tiles_n = (N + TN - 1) / TN;
-  p.tiles_m_per = (rows + TM - 1) / TM;
-  const int tiles_m = nb * p.tiles_m_per;
-  const int tiles = p.tiles_n * tiles_m;
-  // band height: an XCD's share of about tiles/8 tiles covers ~band token tiles and
-  // ~share/band channel tiles; weight rows per channel tile (TN) are worth TN/TM
-  // token tiles, so the square in bytes has band ~ sqrt(share * TN / TM)
-  const double share = (tiles + 7) / 8;
-  const int band = (int)(sqrt(share * TN / TM) + 0.5);
-  p.band = band < 1 ? 1 : (band > tiles_m ? tiles_m : band);
-  const int last = tiles_m - (tiles_m - 1) / p.band * p.band;  // token tiles of the last band
-  p.dv_band_span = make_div((uint32_t)(p.band * p.tiles_n));
-  p.dv_band = make_div((uint32_t)p.band);
-  p.dv_last_band = make_div((uint32_t)last);
-  p.dv_tiles_m_per = make_div((uint32_t)p.tiles_m_per);
-  return tiles;
+  p.grid = tile_grid(nb, rows, N, TN, TM);
+  return p.grid.tiles_n * p.grid.tiles_m;
 }
 
 static void fill_dest(GemmArgs& a, const RunShape& rs, const Workspace& ws, int8_t* y) {

@@ -38,17 +38,27 @@ constexpr int BUF_WORD3 = 0x00020000;  // buffer resource word 3 for gfx9-family
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 // Division by a divisor known only at launch, in integers: the compiler's lowering of a
-// 32-bit division uses a floating-point reciprocal.  With m = floor(2^32 / d) + 1,
-// floor(x / d) = mulhi(x, m) exactly whenever x d < 2^32 (the error term x (m - 2^32/d)
-// / 2^32 stays below 1/d, the smallest gap to the next multiple); d = 1 has m = 0 and
-// passes x, through a select rather than a branch (no load waits on another).
-struct DivU {
-  uint32_t d, m;
+// 32-bit division uses a floating-point reciprocal.  With s = ceil(log2 d) and
+// m = floor(2^(31+s) / d) + 1 (in (2^31, 2^32)), floor(x / d) = floor(x m / 2^(31+s)) for every
+// x < 2^31: m d exceeds 2^(31+s) by at most d <= 2^s, so x m / 2^(31+s) exceeds x / d by less
+// than 1/d, the smallest gap to the next multiple.  (A multiplier over 2^32 without the shift
+// is exact only while x d < 2^32, which the tile counts of accepted calls exceed.)
+struct DivM {
+  uint32_t m, s;
 };
-inline DivU make_div(uint32_t d) { return DivU{d, d <= 1 ? 0u : (uint32_t)((1ull << 32) / d + 1)}; }
-__device__ __forceinline__ uint32_t div_u(uint32_t x, const DivU& v) {
-  return __umulhi(x, v.m) + (v.m == 0u ? x : 0u);
+struct DivU {
+  uint32_t d;
+  DivM by;
+};
+inline DivU make_div(uint32_t d) {
+  uint32_t s = 0;
+  while (((uint64_t)1 << s) < d) ++s;
+  return DivU{d, DivM{(uint32_t)(((uint64_t)1 << (31 + s)) / d + 1), s}};
 }
+__host__ __device__ __forceinline__ uint32_t div_u(uint32_t x, const DivM& v) {
+  return (uint32_t)((uint64_t)(x << 1) * v.m >> 32) >> v.s;
+}
+__host__ __device__ __forceinline__ uint32_t div_u(uint32_t x, const DivU& v) { return div_u(x, v.by); }
 inline int t_aligned(int T) { return round_up(T, KCHUNK); }
 inline int p_rows(int T_al) { return P_PADLO + 2 * T_al + P_PADHI; }
 // Row of table row 0: the smallest value >= P_PADLO with (p_base + T - 1) % 16 == 0.

@@ -1,0 +1,23 @@
+"""Builds host_plans.cpp (the kernels' launch planning as host functions) and loads it."""
+
+import ctypes as C
+import os
+import subprocess
+
+from paper_2609_30846_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+def load(work_dir):
+    """The host functions, compiled into ``work_dir`` (no device code, no GPU needed)."""
+    out = os.path.join(work_dir, "host_plans.so")
+    subprocess.run([B.HIPCC, "-x", "hip", "--offload-host-only", "-O2", "-std=c++20", "-fPIC", "-shared", "-I", B.CSRC,
+                    "-I", os.path.join(B.ROOT, "include"), os.path.join(HERE, "host_plans.cpp"), "-o", out],
+                   check=True, capture_output=True, text=True)
+    lib = C.CDLL(out)
+    lib.tile_grid_fault.argtypes = [C.c_int] * 5
+    lib.tile_grid_fault.restype = C.c_int64
+    lib.div_fault.argtypes = [C.c_uint32, C.c_void_p, C.c_int64]
+    lib.div_fault.restype = C.c_int64
+    return lib
