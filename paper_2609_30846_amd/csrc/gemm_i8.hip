@@ -456,7 +456,7 @@ __global__ __launch_bounds__(64 * NWAVE, NWAVE == 8 ? 1 : 2) void gemm_i8_requan
       dst = o_p + ((size_t)hd * o_prows << dks);
       kk = nb & DKm;
     } else {
-      dst = o_y + (size_t)ub * rows * N + nb;
+      dst = o_y + ((size_t)ub * rows + tw0) * N + nb;  // the token offset in 64 bits: an output may pass 4 GiB
     }
     // the tile-local channel of element e: with rows as tokens (V^T) the column, else
     // row g * 8 + half * 4 + e' of element e = 4g + e'
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(64 * NWAVE, NWAVE == 8 ? 1 : 2) void gemm_i8_requan
     } else {
       tl = tw0 + col;
       tmax = rows;
-      off0 = mode == OUT_ROWMAJOR ? (uint32_t)(tl * N + half * 16)
+      off0 = mode == OUT_ROWMAJOR ? (uint32_t)(col * N + half * 16)
                                   : (uint32_t)frag_off((mode == OUT_POS ? o_pbase : 0) + tl, kk + half * 16);
     }
     const uint32_t jstep = mode == OUT_ROWMAJOR ? 32u * (uint32_t)N : 2u << (dks + 4);
@@ -662,16 +662,16 @@ hipError_t launch_pos_projection(const RunShape& rs, const Weights& w, int8_t* p
   return launch_best<EPI_PLAIN>(rs.d, 32, tiles_of, fill, st, LaunchEv{});
 }
 
-// A row-major product of nb x rows tokens (K -> N), `setup` filling the epilogue's arguments.
+// A row-major product of `rows` tokens (K -> N), `setup` filling the epilogue's arguments.
 template <int EPI, typename Setup>
-static hipError_t launch_rowmajor(const int8_t* x, int nb, int rows, int N, int K, const int8_t* w, const Requant& rq,
+static hipError_t launch_rowmajor(const int8_t* x, int rows, int N, int K, const int8_t* w, const Requant& rq,
                                   int8_t* y, Setup setup, hipStream_t st, const LaunchEv& ev) {
-  auto tiles_of = [&](int tn, int tm) { return nb * ceil_div(rows, tm) * ceil_div(N, tn); };
+  auto tiles_of = [&](int tn, int tm) { return ceil_div(rows, tm) * ceil_div(N, tn); };
   auto fill = [&](GemmArgs& a, int tn, int tm) {
     a.y = y;
     a.nprob = 1;
     setup(a);
-    return add_problem(a, 0, x, w, rq, nb, rows, N, K, OUT_ROWMAJOR, 0, tn, tm);
+    return add_problem(a, 0, x, w, rq, 1, rows, N, K, OUT_ROWMAJOR, 0, tn, tm);
   };
   return launch_best<EPI>(K, 32, tiles_of, fill, st, ev);
 }
@@ -686,15 +686,13 @@ static void set_residual(GemmArgs& a, const int8_t* z, int m_z, int m_y, int shi
 
 hipError_t launch_out_projection(const RunShape& rs, const Weights& w, const Workspace& ws, int8_t* y,
                                  hipStream_t st, const LaunchEv& ev, const Residual* res, const int8_t* z1) {
-  // the utterances' rows are contiguous on both sides, so tiles may straddle them (while the
-  // kernel's 32-bit offsets reach)
-  const bool flat = (int64_t)rs.B * rs.T * rs.d < ((int64_t)1 << 31);
-  const int nb = flat ? 1 : rs.B, rows = flat ? rs.B * rs.T : rs.T;
+  // the utterances' rows are contiguous on both sides, so tiles may straddle them
+  const int rows = rs.B * rs.T;
   if (res)
     return launch_rowmajor<EPI_RESID>(
-        ws.ctx, nb, rows, rs.d, rs.d, w.w_out, w.rq_out, y,
+        ws.ctx, rows, rs.d, rs.d, w.w_out, w.rq_out, y,
         [&](GemmArgs& a) { set_residual(a, z1, res->m_z, res->m_y, res->shift_r); }, st, ev);
-  return launch_rowmajor<EPI_PLAIN>(ws.ctx, nb, rows, rs.d, rs.d, w.w_out, w.rq_out, y, [](GemmArgs&) {}, st, ev);
+  return launch_rowmajor<EPI_PLAIN>(ws.ctx, rows, rs.d, rs.d, w.w_out, w.rq_out, y, [](GemmArgs&) {}, st, ev);
 }
 
 // ---------------------------------------------------------------------------
@@ -723,19 +721,19 @@ hipError_t launch_swish_table(uint8_t* tab, long long q_c, long long q_1, long l
 
 hipError_t launch_ffn_up(const int8_t* x, int rows, int d, int d_ff, const int8_t* w1, const Requant& rq1,
                          const uint8_t* swtab, int8_t* o, hipStream_t st) {
-  return launch_rowmajor<EPI_SWISH>(x, 1, rows, d_ff, d, w1, rq1, o, [&](GemmArgs& a) { a.swtab = swtab; }, st,
+  return launch_rowmajor<EPI_SWISH>(x, rows, d_ff, d, w1, rq1, o, [&](GemmArgs& a) { a.swtab = swtab; }, st,
                                     LaunchEv{});
 }
 
 hipError_t launch_linear_resid(const int8_t* x, int rows, int N, int K, const int8_t* w, const Requant& rq,
                                const int8_t* z, int m_z, int m_y, int shift_r, int8_t* z_out, hipStream_t st) {
-  return launch_rowmajor<EPI_RESID>(x, 1, rows, N, K, w, rq, z_out,
+  return launch_rowmajor<EPI_RESID>(x, rows, N, K, w, rq, z_out,
                                     [&](GemmArgs& a) { set_residual(a, z, m_z, m_y, shift_r); }, st, LaunchEv{});
 }
 
 hipError_t launch_linear(const int8_t* x, int rows, int K, int N, const int8_t* w, const Requant& rq, int8_t* y,
                          hipStream_t st) {
-  return launch_rowmajor<EPI_PLAIN>(x, 1, rows, N, K, w, rq, y, [](GemmArgs&) {}, st, LaunchEv{});
+  return launch_rowmajor<EPI_PLAIN>(x, rows, N, K, w, rq, y, [](GemmArgs&) {}, st, LaunchEv{});
 }
 
 // one thread per 16-byte piece of the destination

@@ -1,5 +1,5 @@
 """Feed-forward calls of millions of rows, whose tile indices leave the range of a 32-bit
-reciprocal product: every row against the same rows run in parts, and rows spread over the
+reciprocal product or whose outputs pass 4 GiB: every row against the same rows run in parts, and rows spread over the
 call (the last ones among them) against the CPU oracle.  The module works row by row."""
 
 import numpy as np
@@ -11,8 +11,8 @@ from workloads import make_ffn
 pytestmark = pytest.mark.gpu
 
 
-# rows of 64 -> 256 channels in more than 2^16 token tiles
-@pytest.mark.parametrize("rows,d,d_ff", [(4692372, 64, 256)])
+# rows of 64 -> 256 channels in more than 2^16 token tiles; an output of more than 2^32 bytes
+@pytest.mark.parametrize("rows,d,d_ff", [(4692372, 64, 256), (4200001, 1024, 64)])
 def test_many_rows(gpu_lib, rows, d, d_ff):
     import torch
 
