@@ -66,10 +66,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 enum OutMode { OUT_QKV = 0, OUT_POS = 1, OUT_ROWMAJOR = 2 };
-// Epilogues of row-major outputs: the requantized int8 values themselves, the residual
-// add of Eq. 2 (with z1 laid out as the output), or the integer Swish of Eq. 12 and
-// its requantization, applied through a 256-entry table indexed by the biased code.
-enum Epilogue { EPI_PLAIN = 0, EPI_RESID = 1, EPI_SWISH = 2 };
 
 struct GemmProblem {
   const int8_t* x;      // [nb][rows][K] activations
@@ -567,53 +563,19 @@ static hipError_t launch_gemm(GemmArgs& a, int tiles, hipStream_t st, const Laun
                               st, ev, a);
 }
 
-// The tile shapes (channels x tokens; four waves, the first eight) and the time model that picks one
-// for a launch: ceil(tiles / CUs) tiles pass through the busiest CU, each costing `fixed`
-// (its first operands and the epilogue: plain, with the residual add, with the Swish) plus
-// `per_k` per 1024 bytes of K, in microseconds fitted to launches of 16 .. 23000 tokens with
-// K = 256 .. 4096 and N = 256 .. 4096 (median error 3 %, and nine picks of ten within 5 % of
-// the fastest shape).  Large tiles re-use their operands best, small ones spread a short
-// call over the chip: 125 tokens x 4096 -> 1024 take 7.8 us in 128 x 32 tiles and 27 us in
-// 256 x 128 ones, 23000 tokens 88 us in the latter and 170 us in the former; 2500 tokens
-// x 1024 -> 4096 are fastest in between (128 x 64, 15.9 us against 17.3 and 21.6 us).
-struct TileShape {
-  int tn, tm;
-  double fixed[3], per_k;
-};
-constexpr TileShape kTiles[] = {{256, 256, {4.5, 7.0, 5.5}, 10.2},
-                                {256, 128, {2.2, 4.1, 2.8}, 5.2},
-                                {256, 64, {1.3, 2.1, 1.45}, 2.9},
-                                {128, 64, {0.52, 0.78, 0.62}, 1.92},
-                                {64, 64, {0.39, 0.46, 0.41}, 1.47},
-                                {128, 32, {0.34, 0.43, 0.31}, 1.40}};
-constexpr int kGemmCUs = 256;
-
 template <int I, int EPI>
 static hipError_t launch_shape(GemmArgs& a, int tiles, hipStream_t st, const LaunchEv& ev) {
   return launch_gemm<kTiles[I].tn, kTiles[I].tm, kTiles[I].tm == 256 ? 8 : 4, kTiles[I].tn == 64 ? 2 : 4, EPI>(a, tiles, st,
                                                                                                                ev);
 }
 
-// Launches with the cheapest shape: tiles_of(tn, tm) counts a shape's tiles, fill(args, tn, tm)
-// adds the problems (all of contraction length K) and returns the same count.  min_tm: 64
-// where V^T is written (whole 64-key blocks).
-template <int EPI, typename Count, typename Fill>
-static hipError_t launch_best(int K, int min_tm, Count tiles_of, Fill fill, hipStream_t st, const LaunchEv& ev) {
-  int best = -1;
-  double best_t = 0.0;
-  for (int i = 0; i < 6; ++i) {
-    const TileShape& s = kTiles[i];
-    if (s.tm < min_tm) continue;
-    const long rounds = (tiles_of(s.tn, s.tm) + kGemmCUs - 1) / kGemmCUs;
-    // one 256 x 256 workgroup fills a CU: with more than one round its first fetch and
-    // epilogue are uncovered (23000 tokens x 1024 -> 4096, six rounds: 120 us against 106 us)
-    if (s.tm == 256 && rounds > 1) continue;
-    const double t = (double)rounds * (s.fixed[EPI] + s.per_k * K / 1024.0);
-    if (best < 0 || t < best_t) {
-      best = i;
-      best_t = t;
-    }
-  }
+// Launches the products of `dims` (all of contraction length K) with the shape that
+// pick_shape takes; fill(args, tn, tm) adds them and returns their tiles.  min_tm: 64 where V^T
+// is written (whole 64-key blocks).
+template <int EPI, typename Fill>
+static hipError_t launch_best(const GemmDims* dims, int n, int K, int min_tm, Fill fill, hipStream_t st,
+                              const LaunchEv& ev) {
+  const int best = pick_shape(dims, n, K, min_tm, EPI);
   GemmArgs a{};
   const int tiles = fill(a, kTiles[best].tn, kTiles[best].tm);
   switch (best) {
@@ -626,15 +588,9 @@ static hipError_t launch_best(int K, int min_tm, Count tiles_of, Fill fill, hipS
   }
 }
 
-static long ceil_div(long a, long b) { return (a + b - 1) / b; }
-
 hipError_t launch_projections(const RunShape& rs, const Weights& w, const Workspace& ws, const int8_t* x,
                               const int8_t* pos_table, hipStream_t st, const LaunchEv& ev) {
-  auto tiles_of = [&](int tn, int tm) {
-    long t = rs.B * ceil_div(rs.T, tm) * ceil_div(3 * rs.d, tn);
-    if (pos_table) t += ceil_div(2 * rs.T - 1, tm) * ceil_div(rs.d, tn);
-    return t;
-  };
+  const GemmDims dims[2] = {{rs.B, rs.T, 3 * rs.d}, {1, 2 * rs.T - 1, rs.d}};
   auto fill = [&](GemmArgs& a, int tn, int tm) {
     fill_dest(a, rs, ws, nullptr);
     int tiles = add_problem(a, 0, x, w.w_qkv, w.rq_qkv, rs.B, rs.T, 3 * rs.d, rs.d, OUT_QKV, 0, tn, tm);
@@ -645,7 +601,7 @@ hipError_t launch_projections(const RunShape& rs, const Weights& w, const Worksp
     }
     return tiles;
   };
-  return launch_best<EPI_PLAIN>(rs.d, KCHUNK, tiles_of, fill, st, ev);
+  return launch_best<EPI_PLAIN>(dims, pos_table ? 2 : 1, rs.d, KCHUNK, fill, st, ev);
 }
 
 hipError_t launch_pos_projection(const RunShape& rs, const Weights& w, int8_t* p, const int8_t* pos_table,
@@ -653,27 +609,27 @@ hipError_t launch_pos_projection(const RunShape& rs, const Weights& w, int8_t* p
   Workspace ws{};
   ws.p = p;
   const int rows = 2 * rs.T - 1;
-  auto tiles_of = [&](int tn, int tm) { return ceil_div(rows, tm) * ceil_div(rs.d, tn); };
+  const GemmDims dims{1, rows, rs.d};
   auto fill = [&](GemmArgs& a, int tn, int tm) {
     fill_dest(a, rs, ws, nullptr);
     a.nprob = 1;
     return add_problem(a, 0, pos_table, w.w_pos, w.rq_pos, 1, rows, rs.d, rs.d, OUT_POS, 0, tn, tm);
   };
-  return launch_best<EPI_PLAIN>(rs.d, 32, tiles_of, fill, st, LaunchEv{});
+  return launch_best<EPI_PLAIN>(&dims, 1, rs.d, 32, fill, st, LaunchEv{});
 }
 
 // A row-major product of `rows` tokens (K -> N), `setup` filling the epilogue's arguments.
 template <int EPI, typename Setup>
 static hipError_t launch_rowmajor(const int8_t* x, int rows, int N, int K, const int8_t* w, const Requant& rq,
                                   int8_t* y, Setup setup, hipStream_t st, const LaunchEv& ev) {
-  auto tiles_of = [&](int tn, int tm) { return ceil_div(rows, tm) * ceil_div(N, tn); };
+  const GemmDims dims{1, rows, N};
   auto fill = [&](GemmArgs& a, int tn, int tm) {
     a.y = y;
     a.nprob = 1;
     setup(a);
     return add_problem(a, 0, x, w, rq, 1, rows, N, K, OUT_ROWMAJOR, 0, tn, tm);
   };
-  return launch_best<EPI>(K, 32, tiles_of, fill, st, ev);
+  return launch_best<EPI>(&dims, 1, K, 32, fill, st, ev);
 }
 
 static void set_residual(GemmArgs& a, const int8_t* z, int m_z, int m_y, int shift_r) {

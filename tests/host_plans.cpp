@@ -33,3 +33,10 @@ extern "C" int64_t div_fault(uint32_t d, const uint32_t* xs, int64_t n) {
     if (div_u(xs[i], v) != xs[i] / d) return xs[i];
   return -1;
 }
+
+// The tile shape a launch of n products {nb, rows, N} of contraction length K takes.
+extern "C" void gemm_shape(const int* dims, int n, int K, int min_tm, int epi, int* tn, int* tm) {
+  const int i = pick_shape((const GemmDims*)dims, n, K, min_tm, epi);
+  *tn = kTiles[i].tn;
+  *tm = kTiles[i].tm;
+}

@@ -20,4 +20,17 @@ def load(work_dir):
     lib.tile_grid_fault.restype = C.c_int64
     lib.div_fault.argtypes = [C.c_uint32, C.c_void_p, C.c_int64]
     lib.div_fault.restype = C.c_int64
+    lib.gemm_shape.argtypes = [C.c_void_p] + [C.c_int] * 4 + [C.POINTER(C.c_int)] * 2
+    lib.gemm_shape.restype = None
     return lib
+
+
+PLAIN, RESID, SWISH = range(3)  # Epilogue of gemm_tiles.h
+
+
+def gemm_shape(lib, products, K, epilogue, min_tm=32):
+    """(channels, tokens) of the tiles of one launch of ``products`` [(nb, rows, N), ...]."""
+    flat = [v for p in products for v in p]
+    tn, tm = C.c_int(), C.c_int()
+    lib.gemm_shape((C.c_int * len(flat))(*flat), len(products), K, min_tm, epilogue, C.byref(tn), C.byref(tm))
+    return tn.value, tm.value
