@@ -40,3 +40,11 @@ extern "C" void gemm_shape(const int* dims, int n, int K, int min_tm, int epi, i
   *tn = kTiles[i].tn;
   *tm = kTiles[i].tm;
 }
+
+// The attention core's plan for B x H (utterance, head) pairs of T frames: key splits, tiles per
+// wave and query blocks of the first and the second shape, and whether two workgroups share a CU.
+extern "C" void attn_shape(int d_k, int T, int64_t pairs, int* out) {
+  const AttnPlan p = attn_plan(d_k, t_aligned(T), (long)pairs, T);
+  const int v[7] = {p.c1.ksplit, p.c1.ntl, p.nqb1, p.c2.ksplit, p.c2.ntl, p.nqb2, p.dense};
+  for (int i = 0; i < 7; ++i) out[i] = v[i];
+}

@@ -1,7 +1,9 @@
-"""The attention core with two workgroups on a CU (short utterances in batches large
-enough to give every CU more than one): both workgroup shapes, the longest utterance of
-which two fit (640 frames for 64 queries), one past it, ragged lengths and both score
-forms, against the CPU oracle."""
+"""The attention core in batches of short utterances, where two workgroups may share a CU:
+paired 64-query (four key splits) and 32-query (eight) workgroups, at d_k 128 in the kernel
+compiled for half the registers and at d_k 64 in the ordinary one, from one 64-key chunk to
+many, the longest utterance of which two 64-query ones fit (704 frames) and one past it, and
+the unpaired plans around them; ragged lengths and both score forms, against the CPU
+oracle.  The plan of each case is asserted on the CPU, by test_attention_plan_host.py."""
 
 import numpy as np
 import pytest
@@ -13,8 +15,12 @@ from workloads.generate import ConfigShape
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,T,d,H", [(34, 33, 1024, 8), (40, 130, 256, 2), (11, 375, 1024, 8), (64, 61, 512, 8), (30, 640, 256, 2),
-                                     (30, 641, 256, 2), (9, 1030, 256, 2)])
+CASES = [(34, 33, 1024, 8), (40, 130, 256, 2), (11, 375, 1024, 8), (64, 61, 512, 8), (30, 640, 256, 2), (30, 641, 256, 2),
+         (9, 1030, 256, 2), (80, 80, 256, 2), (12, 1020, 256, 2), (10, 1216, 256, 2), (40, 300, 256, 2),
+         (18, 704, 256, 2), (18, 705, 256, 2), (80, 80, 256, 4), (40, 300, 256, 4)]
+
+
+@pytest.mark.parametrize("B,T,d,H", CASES)
 def test_pairs(gpu_lib, B, T, d, H):
     import torch
 
