@@ -241,7 +241,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
   // SPILL: the first nsp chunks' scores go through the workgroup's buffer, in parts of at most
   // `sp` chunks (each computed in LDS and copied out); chunks nsp .. nkc - 1 stay in LDS
   const int nsp = SPILL ? max(0, nkc - a.part_chunks) : 0;
-  const int sp = SPILL ? (nsp > a.part_chunks ? (nsp + 1) / 2 : nsp) : 0;  // two parts reach ATTN_MAX_T
+  const int sp = SPILL ? (nsp > a.part_chunks ? (nsp + 1) / 2 : nsp) : 0;  // two parts reach past ATTN_MAX_T
   uint8_t* const spill = SPILL ? a.spill + (size_t)blockIdx.x * a.spill_stride : nullptr;
   int c_begin, c_end;
   split(nkc - nsp, P2_OLDER, &c_begin, &c_end);

@@ -219,7 +219,7 @@ extern "C" int ipk_relpos_attn_create(const ipk_relpos_attn_desc* desc, ipk_relp
   int st = validate_desc(desc);
   if (st != IPK_OK) return st;
   if (desc->max_T > ATTN_MAX_T)
-    return fail(IPK_ERR_UNSUPPORTED, "max_T=%d does not fit the on-chip score rows (%d frames)", desc->max_T, ATTN_MAX_T);
+    return fail(IPK_ERR_UNSUPPORTED, "max_T=%d is above the attention core's %d frames", desc->max_T, ATTN_MAX_T);
 
   ipk_relpos_attn* h = new (std::nothrow) ipk_relpos_attn();
   if (!h) return fail(IPK_ERR_OUT_OF_MEMORY, "host allocation failed");

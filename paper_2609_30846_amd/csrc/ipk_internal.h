@@ -229,8 +229,8 @@ struct AttnPlan {
   bool dense = false;  // two workgroups of c1 per CU
 };
 AttnPlan attn_plan(int DK, int T_al, long bh_count, int T);
-// Longest utterance of the attention core (its spilling workgroups take the keys in three
-// parts at most).
+// Longest utterance of the attention core.  Its spilling workgroups take the keys in three parts
+// at most (11904 frames would fit them); the bound is the documented and tested one.
 constexpr int ATTN_MAX_T = 8000;
 // Bytes of the attention core's spill buffers for utterances of up to T_al keys (0 when the
 // score rows fit LDS).

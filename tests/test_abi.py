@@ -347,15 +347,14 @@ def test_generated_module_constants_pass_validation_ranges():
                 assert int(q.max()) * cv.m_sw + (1 << (cv.shift_sw - 1)) < (1 << 62)
 
 
-def test_create_rejects_max_T_beyond_the_score_rows():
-    """The attention core keeps every score row of a workgroup on chip: with one 16-query
-    tile per wave the longest supported utterance is 8000 frames (125 chunks of 64) for
-    d_k 64 and 128; one frame more is IPK_ERR_UNSUPPORTED before any device call."""
+def test_create_rejects_max_T_beyond_the_attention_core():
+    """The attention core takes utterances of up to 8000 frames (125 chunks of 64) for d_k 64
+    and 128; one frame more is IPK_ERR_UNSUPPORTED before any device call."""
     for dk, H in ((64, 4), (128, 2)):
         d, keep = _valid_desc()
         d.d_k, d.n_heads, d.max_T = dk, H, 8001
         assert _create_status(d) == ipk.IPK_ERR_UNSUPPORTED
-        assert "on-chip score rows" in ipk.last_error()
+        assert "max_T=8001" in ipk.last_error() and "8000 frames" in ipk.last_error()
 
 
 def test_binding_rejects_bad_tensors_before_the_library():

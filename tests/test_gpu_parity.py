@@ -204,9 +204,10 @@ def test_run_argument_errors(gpu_lib):
 
 
 @pytest.mark.parametrize("T,lengths", [(3969, [3969, 3000]), (4500, [4500, 4463])])
-def test_single_tile_workgroups(gpu_lib, T, lengths):
-    """Utterances longer than the 32- and 48-query workgroups' score rows allow run on
-    16-query workgroups (one tile per wave): just past that limit and beyond, d_k 64 and
+def test_spilling_block_loop(gpu_lib, T, lengths):
+    """Utterances longer than the score rows that fit on chip (3968 frames), in launches of
+    more blocks than CUs: each spilling workgroup carries on from block to block, its tables,
+    score rows and buffer overwritten each time.  Just past the limit and beyond, d_k 64 and
     128, ragged lengths."""
     import dataclasses
 
@@ -217,7 +218,7 @@ def test_single_tile_workgroups(gpu_lib, T, lengths):
                                     name="tiny")
         for regime in ("literal", "calibrated"):
             blk = generate.make_block(shape, T, np.random.default_rng(T + d + H), regime, lengths=lengths)
-            print(f"[parity] single-tile workgroups T={T} d_k={d // H} {regime}", flush=True)
+            print(f"[parity] spilling block loop T={T} d_k={d // H} {regime}", flush=True)
             g = _run_gpu(gpu_lib, blk)
             y = core.relpos_attn(blk)
             assert _first_mismatch(g["y"], y) is None, (T, d // H, regime, _first_mismatch(g["y"], y))
@@ -248,8 +249,8 @@ def test_largest_batch(gpu_lib, T):
 
 
 def test_longest_supported_T(gpu_lib):
-    """The longest utterance the on-chip score rows allow (create rejects a longer
-    max_T with IPK_ERR_UNSUPPORTED), d_k = 64 and 128."""
+    """The longest utterance the attention core takes (create rejects a longer max_T with
+    IPK_ERR_UNSUPPORTED), d_k = 64 and 128."""
     import dataclasses
 
     from workloads import generate
