@@ -1,11 +1,11 @@
 // Relative-position attention core of the integer MHSA block (Sec. 3.1).
 //
 // Work split: a workgroup of ATTN_WAVES waves owns (utterance b, head h, WGQ
-// consecutive queries).  Its int8 score rows stay in LDS (never in HBM), laid out in
-// 16-key blocks: block j/16 holds the WGQ rows' 16 scores of those keys, 16 bytes per
-// row, so the row of query r and key j sits at byte (j/16) WGQ 16 + 16 r + j % 16.
-// The host picks the workgroup shape per launch from the LDS the rows need and the
-// rounds of workgroups over the CUs.
+// consecutive queries).  Its int8 score rows stay in LDS (up to 3968 frames; longer
+// utterances below), laid out in 16-key blocks: block j/16 holds the WGQ rows' 16 scores
+// of those keys, 16 bytes per row, so the row of query r and key j sits at byte
+// (j/16) WGQ 16 + 16 r + j % 16.  The host picks the workgroup shape per launch from the
+// LDS the rows need and the rounds of workgroups over the CUs.
 //
 // Phase 1 (scores), per 16-key step, with v_mfma_i32_16x16x64_i8 (queries on MFMA
 // rows).  KSPLIT waves share a query set of NTL 16-query tiles (every K and P fragment
@@ -67,12 +67,13 @@ struct AttnArgs {
   int8_t* ctx;
   Lengths lens;
   int T, T_al, H, d, p_rows, p_base;
-  int nqb;        // query blocks per (utterance, head) of the first segment
-  DivU dv_nqb, dv_nqb2, dv_H;  // the block decomposition's divisors
+  // the block decomposition's divisors: query blocks per (utterance, head) of the first and the
+  // second segment, heads
+  DivU dv_nqb, dv_nqb2, dv_H;
   int xcd_group;  // keep each (utterance, head) on one XCD
   // second segment of a two-shape grid: blocks from seg2_block on cover the queries
-  // from seg2_q0 on, nqb2 blocks per (utterance, head), with the second shape
-  int seg2_block, seg2_q0, nqb2;
+  // from seg2_q0 on with the second shape
+  int seg2_block, seg2_q0;
   // fused score, 32-bit path: t = mc24 c + mp24 p + bias32, code in bits 16..23
   int32_t mc24, mp24, bias32;
   // fused score, 64-bit path: t = m_c c + m_p p + bias64, code = t >> shift_s
@@ -299,184 +300,184 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, unsigned char* sme
   // phase 1 over keys k_first (a multiple of 64) .. k_end - 1, whose scores start at the
   // beginning of the LDS rows
   auto phase1 = [&](const int k_first, const int k_end) {
-  // the 16-key steps that hold a valid key are split over the key parts
-  const int nst = (k_end - k_first + 15) >> 4;
-  int j_begin, j_stop;
-  split(nst, P1_OLDER, &j_begin, &j_stop);
-  j_begin = k_first + 16 * j_begin;
-  j_stop = k_first + 16 * j_stop;
-  const int j_full = max(j_begin, min(j_stop, k_end & ~15));  // steps below this are unmasked
-  if (active && j_begin < j_stop) {
-    const uint32_t frag = (uint32_t)frag_off;
-    v4i qf[NTL][NKS];
-#pragma unroll
-    for (int t = 0; t < NTL; ++t) {
-      // a tile past the padded sequence (last workgroup, T_al not a multiple of the
-      // workgroup's queries) re-reads the last tile: its rows are never stored
-      const int qrow = min(q0 + 16 * t, T_al - 16);
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) qf[t][s] = *(const v4i*)(Qh + (size_t)qrow * DK + frag + s * 1024);
-    }
-    bool take_hi[4];
-    int src_addr[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int arow = 4 * g + i;
-      take_hi[i] = (col + arow) < 16;                    // as a source lane
-      src_addr[i] = (g * 16 + ((col - arow) & 15)) * 4;  // as a destination lane
-    }
-    // a lane's score of query row 4g + i of tile t and key j0 + col is byte col of that
-    // row's 16 bytes in block j0 / 16: the row and tile offsets are immediates
-    const uint32_t sdst0 = base + (uint32_t)((ROWS * qset + 4 * g) * 16 + col);
-
-    // K and the position table are streamed with raw buffer loads: the lane's offset in
-    // a fragment is fixed and the step's offset is a scalar, so no vector address
-    // arithmetic is spent per load.  Table row of (query q0, key j0) is
-    // j0 - q0 + T - 1; tile t sits 16 t rows lower.  Every offset stays inside the
-    // padded buffers (the table keeps P_PADLO rows below row 0).
-    const __amdgpu_buffer_rsrc_t kres =
-        __builtin_amdgcn_make_buffer_rsrc((void*)Kh, (short)0, T_al * DK, BUF_WORD3);
-    const __amdgpu_buffer_rsrc_t pres =
-        __builtin_amdgcn_make_buffer_rsrc((void*)Ph, (short)0, a.p_rows * DK, BUF_WORD3);
-    int koff = __builtin_amdgcn_readfirstlane(j_begin * DK);
-    int poff = __builtin_amdgcn_readfirstlane((a.p_base + j_begin - q0 + T - 1) * DK);
-    auto ldk = [&](int off, int s) { return (v4i)__builtin_amdgcn_raw_buffer_load_b128(kres, frag + s * 1024, off, 0); };
-    auto ldp = [&](int off, int s) { return (v4i)__builtin_amdgcn_raw_buffer_load_b128(pres, frag + s * 1024, off, 0); };
-    // The rank-1 terms of Eq. 8 come from MFMAs of a 16-row operand whose rows all
-    // equal u (v): their products with a K (P) fragment hold u.K_j (v.P_r) in every
-    // row, which is the accumulator seed the content (position) MFMAs need.  No load
-    // is spent on them.
-    v4i uf[NKS], vf[NKS];
-#pragma unroll
-    for (int s = 0; s < NKS; ++s) {
-      uf[s] = *(const v4i*)(a.u + (size_t)h * DK + s * 64 + g * 16);
-      vf[s] = *(const v4i*)(a.v + (size_t)h * DK + s * 64 + g * 16);
-    }
-    auto rank1 = [&](const v4i* vec, const v4i* fr) {
-      v4i r = (v4i){0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) r = __builtin_amdgcn_mfma_i32_16x16x64_i8(vec[s], fr[s], r, 0, 0, 0);
-      return r;
-    };
-
-    // Register rings over the step phase S = (step index) % RING, all indices static:
-    //  pr[u]:    tile 0's hi-window P fragment of the step with phase u; at phase S
-    //            tile t uses slot (S - t) mod RING (its window is tile 0's window of t
-    //            steps before)
-    //  bv[u]:    the seed v.P_r of that window (all four rows)
-    //  kr[u]:    K fragment of the step with phase u (current, next)
-    //  gr[u][t]: position MFMA results (hi windows) of the step with phase u; a
-    //            step's lo windows are the previous step's hi windows
-    constexpr int RING = NTL;
-    static_assert(NTL > 1, "the current and the next step never share a ring slot");
-    v4i pr[RING][NKS], kr[RING][NKS], gr[RING][NTL], bv[RING];
-    {
-      // tile t's hi window of the first step: tile 0's window 16 t rows lower
-#pragma unroll
+    // the 16-key steps that hold a valid key are split over the key parts
+    const int nst = (k_end - k_first + 15) >> 4;
+    int j_begin, j_stop;
+    split(nst, P1_OLDER, &j_begin, &j_stop);
+    j_begin = k_first + 16 * j_begin;
+    j_stop = k_first + 16 * j_stop;
+    const int j_full = max(j_begin, min(j_stop, k_end & ~15));  // steps below this are unmasked
+    if (active && j_begin < j_stop) {
+      const uint32_t frag = (uint32_t)frag_off;
+      v4i qf[NTL][NKS];
+  #pragma unroll
       for (int t = 0; t < NTL; ++t) {
-        const int u = (RING - t) % RING;
-#pragma unroll
-        for (int s = 0; s < NKS; ++s) pr[u][s] = ldp(poff - 16 * t * DK, s);
+        // a tile past the padded sequence (last workgroup, T_al not a multiple of the
+        // workgroup's queries) re-reads the last tile: its rows are never stored
+        const int qrow = min(q0 + 16 * t, T_al - 16);
+  #pragma unroll
+        for (int s = 0; s < NKS; ++s) qf[t][s] = *(const v4i*)(Qh + (size_t)qrow * DK + frag + s * 1024);
       }
-      // lo windows of the first step: tile t's lo window is tile (t + 1)'s hi window;
-      // the last tile's lies one more window lower
-      v4i plast[NKS];
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) plast[s] = ldp(poff - 16 * NTL * DK, s);
-#pragma unroll
-      for (int t = 0; t < NTL; ++t) bv[(RING - t) % RING] = rank1(vf, pr[(RING - t) % RING]);
-      const v4i bvlast = rank1(vf, plast);
-#pragma unroll
-      for (int t = 0; t < NTL; ++t) {
-        const int u = (RING - t - 1) % RING;  // slot of tile (t + 1)'s hi window
-        v4i gacc = t + 1 < NTL ? bv[u] : bvlast;
-#pragma unroll
-        for (int s = 0; s < NKS; ++s)
-          gacc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][s], t + 1 < NTL ? pr[u][s] : plast[s], gacc, 0, 0, 0);
-        gr[RING - 1][t] = gacc;
+      bool take_hi[4];
+      int src_addr[4];
+  #pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int arow = 4 * g + i;
+        take_hi[i] = (col + arow) < 16;                    // as a source lane
+        src_addr[i] = (g * 16 + ((col - arow) & 15)) * 4;  // as a destination lane
       }
-    }
-#pragma unroll
-    for (int s = 0; s < NKS; ++s) kr[0][s] = ldk(koff, s);
+      // a lane's score of query row 4g + i of tile t and key j0 + col is byte col of that
+      // row's 16 bytes in block j0 / 16: the row and tile offsets are immediates
+      const uint32_t sdst0 = base + (uint32_t)((ROWS * qset + 4 * g) * 16 + col);
 
-    int j0 = j_begin;
-    // One 16-key step at phase S: fetches the next step's K and P fragments (the last
-    // step re-reads its own rows, in bounds), runs the content and position MFMAs of
-    // every tile and turns them into score codes in LDS.
-    auto step = [&](auto Sc, const bool masked) {
-      constexpr int S = decltype(Sc)::value;
-      constexpr int SN = (S + 1) % RING, SP = (S + RING - 1) % RING;
-      const int adv = j0 + 16 < j_stop ? 16 * DK : 0;
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) kr[SN][s] = ldk(koff + adv, s);
-      // seeds: u.K_j of this step's keys (shared by the tiles) and v.P_r of this step's
-      // new window (kept with it in the ring)
-      const v4i uk = rank1(uf, kr[S]);
-      bv[S] = rank1(vf, pr[S]);
-      v4i cs[NTL];
-#pragma unroll
-      for (int t = 0; t < NTL; ++t) {
-        cs[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][0], kr[S][0], uk, 0, 0, 0);
-        gr[S][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][0], pr[(S + RING - t) % RING][0],
-                                                         bv[(S + RING - t) % RING], 0, 0, 0);
+      // K and the position table are streamed with raw buffer loads: the lane's offset in
+      // a fragment is fixed and the step's offset is a scalar, so no vector address
+      // arithmetic is spent per load.  Table row of (query q0, key j0) is
+      // j0 - q0 + T - 1; tile t sits 16 t rows lower.  Every offset stays inside the
+      // padded buffers (the table keeps P_PADLO rows below row 0).
+      const __amdgpu_buffer_rsrc_t kres =
+          __builtin_amdgcn_make_buffer_rsrc((void*)Kh, (short)0, T_al * DK, BUF_WORD3);
+      const __amdgpu_buffer_rsrc_t pres =
+          __builtin_amdgcn_make_buffer_rsrc((void*)Ph, (short)0, a.p_rows * DK, BUF_WORD3);
+      int koff = __builtin_amdgcn_readfirstlane(j_begin * DK);
+      int poff = __builtin_amdgcn_readfirstlane((a.p_base + j_begin - q0 + T - 1) * DK);
+      auto ldk = [&](int off, int s) { return (v4i)__builtin_amdgcn_raw_buffer_load_b128(kres, frag + s * 1024, off, 0); };
+      auto ldp = [&](int off, int s) { return (v4i)__builtin_amdgcn_raw_buffer_load_b128(pres, frag + s * 1024, off, 0); };
+      // The rank-1 terms of Eq. 8 come from MFMAs of a 16-row operand whose rows all
+      // equal u (v): their products with a K (P) fragment hold u.K_j (v.P_r) in every
+      // row, which is the accumulator seed the content (position) MFMAs need.  No load
+      // is spent on them.
+      v4i uf[NKS], vf[NKS];
+  #pragma unroll
+      for (int s = 0; s < NKS; ++s) {
+        uf[s] = *(const v4i*)(a.u + (size_t)h * DK + s * 64 + g * 16);
+        vf[s] = *(const v4i*)(a.v + (size_t)h * DK + s * 64 + g * 16);
       }
-#pragma unroll
-      for (int s = 1; s < NKS; ++s)
-#pragma unroll
+      auto rank1 = [&](const v4i* vec, const v4i* fr) {
+        v4i r = (v4i){0, 0, 0, 0};
+  #pragma unroll
+        for (int s = 0; s < NKS; ++s) r = __builtin_amdgcn_mfma_i32_16x16x64_i8(vec[s], fr[s], r, 0, 0, 0);
+        return r;
+      };
+
+      // Register rings over the step phase S = (step index) % RING, all indices static:
+      //  pr[u]:    tile 0's hi-window P fragment of the step with phase u; at phase S
+      //            tile t uses slot (S - t) mod RING (its window is tile 0's window of t
+      //            steps before)
+      //  bv[u]:    the seed v.P_r of that window (all four rows)
+      //  kr[u]:    K fragment of the step with phase u (current, next)
+      //  gr[u][t]: position MFMA results (hi windows) of the step with phase u; a
+      //            step's lo windows are the previous step's hi windows
+      constexpr int RING = NTL;
+      static_assert(NTL > 1, "the current and the next step never share a ring slot");
+      v4i pr[RING][NKS], kr[RING][NKS], gr[RING][NTL], bv[RING];
+      {
+        // tile t's hi window of the first step: tile 0's window 16 t rows lower
+  #pragma unroll
         for (int t = 0; t < NTL; ++t) {
-          cs[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][s], kr[S][s], cs[t], 0, 0, 0);
-          gr[S][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][s], pr[(S + RING - t) % RING][s], gr[S][t], 0, 0, 0);
+          const int u = (RING - t) % RING;
+  #pragma unroll
+          for (int s = 0; s < NKS; ++s) pr[u][s] = ldp(poff - 16 * t * DK, s);
         }
-      // the last tile's window (slot SN) is consumed: it takes the next step's tile-0 window
-#pragma unroll
-      for (int s = 0; s < NKS; ++s) pr[SN][s] = ldp(poff + adv, s);
-      const bool key_ok = j0 + col < L;
-      lds8* sp = (lds8*)(uintptr_t)(sdst0 + (uint32_t)((j0 - k_first) >> 4) * BLK);
-#pragma unroll
-      for (int t = 0; t < NTL; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int sel = take_hi[i] ? gr[S][t][i] : gr[SP][t][i];
-          const int pt = __builtin_amdgcn_ds_bpermute(src_addr[i], sel);
-          int v;
-          if (WIDE) {
-            // exact in 64 bits: |m c| + |m p| < 2^47
-            const int64_t tt = (int64_t)a.m_c * cs[t][i] + (int64_t)a.m_p * pt + a.bias64;
-            const int64_t q = tt >> a.shift_s;
-            v = q < 1 ? 1 : (q > 255 ? 255 : (int)q);
-          } else {
-            // cs holds c0 + u.K_j: the addend is the rounding and code bias alone
-            int x = mad_i24(a.mp24, pt, a.bias32);
-            asm("" : "+v"(x));  // opaque to the optimizer (keeps the multiply-adds apart), not a scheduling barrier
-            v = mad_i24(a.mc24, cs[t][i], x);
-            v = min(max(v, LOCODE), HICODE);
-          }
-          if (masked && !key_ok) v = LOCODE;
-          mx[t][i] = max(mx[t][i], v);
-          // the code is bits 0..7 (64-bit path) or 16..23 (32-bit path) of v
-          sp[(16 * t + i) * 16] = (uint8_t)(WIDE ? v : (v >> 16));
+        // lo windows of the first step: tile t's lo window is tile (t + 1)'s hi window;
+        // the last tile's lies one more window lower
+        v4i plast[NKS];
+  #pragma unroll
+        for (int s = 0; s < NKS; ++s) plast[s] = ldp(poff - 16 * NTL * DK, s);
+  #pragma unroll
+        for (int t = 0; t < NTL; ++t) bv[(RING - t) % RING] = rank1(vf, pr[(RING - t) % RING]);
+        const v4i bvlast = rank1(vf, plast);
+  #pragma unroll
+        for (int t = 0; t < NTL; ++t) {
+          const int u = (RING - t - 1) % RING;  // slot of tile (t + 1)'s hi window
+          v4i gacc = t + 1 < NTL ? bv[u] : bvlast;
+  #pragma unroll
+          for (int s = 0; s < NKS; ++s)
+            gacc = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][s], t + 1 < NTL ? pr[u][s] : plast[s], gacc, 0, 0, 0);
+          gr[RING - 1][t] = gacc;
         }
       }
-      koff += 16 * DK;
-      poff += 16 * DK;
-      j0 += 16;
-    };
-    // RING unmasked steps per iteration, so that every ring index stays static
-    while (j0 + 16 * RING <= j_full) {
-      step(Phase<0>{}, false);
-      step(Phase<1>{}, false);
-      if constexpr (RING > 2) step(Phase<2 % RING>{}, false);
+  #pragma unroll
+      for (int s = 0; s < NKS; ++s) kr[0][s] = ldk(koff, s);
+
+      int j0 = j_begin;
+      // One 16-key step at phase S: fetches the next step's K and P fragments (the last
+      // step re-reads its own rows, in bounds), runs the content and position MFMAs of
+      // every tile and turns them into score codes in LDS.
+      auto step = [&](auto Sc, const bool masked) {
+        constexpr int S = decltype(Sc)::value;
+        constexpr int SN = (S + 1) % RING, SP = (S + RING - 1) % RING;
+        const int adv = j0 + 16 < j_stop ? 16 * DK : 0;
+  #pragma unroll
+        for (int s = 0; s < NKS; ++s) kr[SN][s] = ldk(koff + adv, s);
+        // seeds: u.K_j of this step's keys (shared by the tiles) and v.P_r of this step's
+        // new window (kept with it in the ring)
+        const v4i uk = rank1(uf, kr[S]);
+        bv[S] = rank1(vf, pr[S]);
+        v4i cs[NTL];
+  #pragma unroll
+        for (int t = 0; t < NTL; ++t) {
+          cs[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][0], kr[S][0], uk, 0, 0, 0);
+          gr[S][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][0], pr[(S + RING - t) % RING][0],
+                                                           bv[(S + RING - t) % RING], 0, 0, 0);
+        }
+  #pragma unroll
+        for (int s = 1; s < NKS; ++s)
+  #pragma unroll
+          for (int t = 0; t < NTL; ++t) {
+            cs[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][s], kr[S][s], cs[t], 0, 0, 0);
+            gr[S][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(qf[t][s], pr[(S + RING - t) % RING][s], gr[S][t], 0, 0, 0);
+          }
+        // the last tile's window (slot SN) is consumed: it takes the next step's tile-0 window
+  #pragma unroll
+        for (int s = 0; s < NKS; ++s) pr[SN][s] = ldp(poff + adv, s);
+        const bool key_ok = j0 + col < L;
+        lds8* sp = (lds8*)(uintptr_t)(sdst0 + (uint32_t)((j0 - k_first) >> 4) * BLK);
+  #pragma unroll
+        for (int t = 0; t < NTL; ++t) {
+  #pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int sel = take_hi[i] ? gr[S][t][i] : gr[SP][t][i];
+            const int pt = __builtin_amdgcn_ds_bpermute(src_addr[i], sel);
+            int v;
+            if (WIDE) {
+              // exact in 64 bits: |m c| + |m p| < 2^47
+              const int64_t tt = (int64_t)a.m_c * cs[t][i] + (int64_t)a.m_p * pt + a.bias64;
+              const int64_t q = tt >> a.shift_s;
+              v = q < 1 ? 1 : (q > 255 ? 255 : (int)q);
+            } else {
+              // cs holds c0 + u.K_j: the addend is the rounding and code bias alone
+              int x = mad_i24(a.mp24, pt, a.bias32);
+              asm("" : "+v"(x));  // opaque to the optimizer (keeps the multiply-adds apart), not a scheduling barrier
+              v = mad_i24(a.mc24, cs[t][i], x);
+              v = min(max(v, LOCODE), HICODE);
+            }
+            if (masked && !key_ok) v = LOCODE;
+            mx[t][i] = max(mx[t][i], v);
+            // the code is bits 0..7 (64-bit path) or 16..23 (32-bit path) of v
+            sp[(16 * t + i) * 16] = (uint8_t)(WIDE ? v : (v >> 16));
+          }
+        }
+        koff += 16 * DK;
+        poff += 16 * DK;
+        j0 += 16;
+      };
+      // RING unmasked steps per iteration, so that every ring index stays static
+      while (j0 + 16 * RING <= j_full) {
+        step(Phase<0>{}, false);
+        step(Phase<1>{}, false);
+        if constexpr (RING > 2) step(Phase<2 % RING>{}, false);
+      }
+      // the rest: fewer than RING steps below j_full, then at most one masked step (j_stop
+      // is at most L rounded up to 16, and j_full at least L rounded down), so at most
+      // RING steps in straight-line code whose ring phases stay static (a loop over them
+      // would move the rings between registers on every pass)
+      if (j0 < j_stop) step(Phase<0>{}, j0 + 16 > j_full);
+      if (j0 < j_stop) step(Phase<1 % RING>{}, j0 + 16 > j_full);
+      if constexpr (RING > 2) {
+        if (j0 < j_stop) step(Phase<2 % RING>{}, j0 + 16 > j_full);
+      }
     }
-    // the rest: fewer than RING steps below j_full, then at most one masked step (j_stop
-    // is at most L rounded up to 16, and j_full at least L rounded down), so at most
-    // RING steps in straight-line code whose ring phases stay static (a loop over them
-    // would move the rings between registers on every pass)
-    if (j0 < j_stop) step(Phase<0>{}, j0 + 16 > j_full);
-    if (j0 < j_stop) step(Phase<1 % RING>{}, j0 + 16 > j_full);
-    if constexpr (RING > 2) {
-      if (j0 < j_stop) step(Phase<2 % RING>{}, j0 + 16 > j_full);
-    }
-  }
   };
   if constexpr (SPILL) {
     for (int c = 0;; c += sp) {
@@ -1112,11 +1113,9 @@ static hipError_t launch_attn_plan(const AttnArgs& args, const AttnPlan& p, int 
   hipError_t e = allow_lds((const void*)kernel, (int)kLdsBudget);
   if (e != hipSuccess) return e;
   AttnArgs a2 = args;
-  a2.nqb = p.nqb1;
   a2.xcd_group = (B * H) % 8 == 0;
   a2.seg2_block = p.nqb1 * B * H;
   a2.seg2_q0 = p.nqb1 * wgq_of(p.c1);
-  a2.nqb2 = p.nqb2;
   a2.dv_nqb = make_div((uint32_t)p.nqb1);
   a2.dv_nqb2 = make_div((uint32_t)(p.nqb2 > 0 ? p.nqb2 : 1));
   a2.dv_H = make_div((uint32_t)H);
@@ -1131,11 +1130,11 @@ static hipError_t launch_attn_spill(const AttnArgs& args, const RunShape& rs, hi
   const hipError_t e = allow_lds((const void*)relpos_attn_spill<DK, NTL, WIDE>, (int)kLdsBudget);
   if (e != hipSuccess) return e;
   AttnArgs a = args;
-  a.nqb = (rs.T + wgq_of(c) - 1) / wgq_of(c);
+  const int nqb = (rs.T + wgq_of(c) - 1) / wgq_of(c);
   a.xcd_group = (rs.B * rs.H) % 8 == 0;
-  a.dv_nqb = make_div((uint32_t)a.nqb);
+  a.dv_nqb = make_div((uint32_t)nqb);
   a.dv_H = make_div((uint32_t)rs.H);
-  a.nblocks = a.nqb * rs.B * rs.H;
+  a.nblocks = nqb * rs.B * rs.H;
   a.part_chunks = part_chunks_of(c);
   a.spill_stride = (uint32_t)spill_stride_of(c, rs.T_al);
   return launch_kernel(relpos_attn_spill<DK, NTL, WIDE>, dim3(std::min(a.nblocks, kNumCUs)), dim3(64 * ATTN_WAVES),

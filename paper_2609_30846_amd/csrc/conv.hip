@@ -39,7 +39,7 @@
 
 namespace ipk {
 
-constexpr int CONV_TAPS = 9, CONV_HALF = 4;
+constexpr int CONV_HALF = 4;      // frames on either side of the nine taps
 constexpr int CONV_WAVES = 16;    // one workgroup per CU: frame quads of the window side by side
 constexpr int CONV_CH = 256;      // channels per tile (four per lane)
 constexpr int CONV_MAXF = 4 * CONV_WAVES - 2 * CONV_HALF;  // output frames per tile at most

@@ -37,9 +37,10 @@
 // 16.9 us from first to last workgroup, and the attention core after it at 2.20 GHz instead
 // of 2.08 GHz on a card that runs into its power limit).
 //
-// Token tiles never straddle two utterances (each utterance is tiled on its own), so
-// every destination layout receives whole aligned 16-byte pieces.  Tiles are dealt
-// to the eight XCDs in contiguous, roughly square groups of the tile grid, so the
+// Token tiles of Q|K|V never straddle two utterances (each is tiled on its own, and V^T is
+// written in whole 64-key blocks); row-major products, the output projection among them, take
+// all their rows as one sequence.  Every destination receives whole aligned 16-byte pieces.
+// Tiles are dealt to the eight XCDs in contiguous, roughly square groups of the tile grid, so the
 // operand rows one XCD touches fit its L2.
 //
 // Epilogue: the requantization y = clamp8(floor((acc m + 2^(n-1)) / 2^n)) in integers.
@@ -50,10 +51,11 @@
 // t = a m' + 2^15, whose clamp to [-127 2^16, 127 2^16 + 2^16 - 1] holds the int8
 // result in byte 2: three full-rate instructions per value, one multiplier register per
 // value, and a byte permute gathers four results into a dword.  Otherwise the value
-// is evaluated in 64-bit integers, its constants read from LDS per value.  Each lane owns 4 consecutive outputs per accumulator group; one
-// exchange with the lane 32 away gives it 16 consecutive bytes, stored with one 16-byte
-// write.  Channel-major V^T is produced by swapping the MFMA operands in the waves whose
-// channels are V, so that its 16-byte pieces run along tokens.
+// is evaluated in 64-bit integers, its constants read from LDS per value.  Each lane owns 4
+// consecutive outputs per accumulator group; one exchange with the lane 32 away gives it 16
+// consecutive bytes, stored with one 16-byte write.  Channel-major V^T is produced by swapping
+// the MFMA operands in the waves whose channels are V, so that its 16-byte pieces run along
+// tokens.
 #include <type_traits>
 #include <utility>
 
