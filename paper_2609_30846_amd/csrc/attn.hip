@@ -1013,7 +1013,9 @@ static double wg_cost(const AttnCfg& c, int T) {
 // times the part that scales with T, from 30 x 200, 16 x 375 and 8 x 500 frames (core 35.9 ->
 // 27.0, 31.5 -> 27.6 and 27.4 -> 23.4 us).  Alone on a CU, as in a last round of at most one per
 // CU, the kernel for at most 128 registers is 8 - 16 % slower than the ordinary one (T = 1000,
-// 256 workgroups: 15.0 us against 13.8; T = 3500: 131 against 113).
+// 256 workgroups: 15.0 us against 13.8; T = 3500: 131 against 113).  At d_k = 64 the ordinary kernels
+// (94 registers) share a CU whatever the plan says, so there the rule only decides which shape
+// runs, and makespan's one workgroup per CU prices the unpaired plans too high.
 static double pairs_time(long count, const AttnCfg& c, int T) {
   const double pair = 1.13 * kWgFixedCost + 2.06 * (wg_cost(c, T) - kWgFixedCost);
   const long full = count / (2 * kNumCUs), rest = count % (2 * kNumCUs);
